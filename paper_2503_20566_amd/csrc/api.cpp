@@ -929,10 +929,12 @@ int sr_build(peps_handle* h, const double* O, const int32_t* block_id, const uin
   if (int st = ensure_device(h)) return st;
   hipStream_t s = (hipStream_t)stream;
   double* ov = (double*)((char*)ws + wl.sr);
-  double* omv = ov + B;
   return hip_status(timed(h, PEPS_K_SR, s, [&] {
-    return launch_sr(h->d, h->t, h->n_params, block_id, valid, O, e_loc, B, mode, v, F, O_mean,
-                     S_or_Sv, ov, omv, s);
+    hipError_t e = launch_sr_sums(h->d, h->t, block_id, valid, O, e_loc, B, F, O_mean, s);
+    if (e != hipSuccess) return e;
+    return mode == SR_MATVEC
+               ? launch_sr_matvec(h->d, h->t, block_id, valid, O, B, O_mean, v, ov, S_or_Sv, s)
+               : launch_sr_dense(h->d, h->t, h->n_params, block_id, valid, O, B, O_mean, S_or_Sv, s);
   }));
 }
 
@@ -978,43 +980,31 @@ int sr_solve(peps_handle* h, const double* O, const int32_t* block_id, const uin
   hipStream_t s = (hipStream_t)stream;
   const int64_t n = h->n_params;
   double* ov = (double*)((char*)ws + wl.sr);
-  double* omv = ov + B;
   double* r = (double*)((char*)ws + wl.cg);
   double* p = r + n;
   double* q = p + n;
   double* sc = q + n;
-  auto matvec = [&](const double* v, double* out) {  // S v (F and <O> rewritten, same values)
-    return timed(h, PEPS_K_SR, s, [&] {
-      return launch_sr(h->d, h->t, n, block_id, valid, O, e_loc, B, SR_MATVEC, v, F, O_mean, out, ov,
-                       omv, s);
-    });
-  };
+  static_assert(kCgScalars <= 2 * (kMaxCgIter + 2), "the workspace holds the scalars and partial sums");
   auto host = [&](const double* src, double* dst, int cnt) {
     hipError_t e = hipMemcpyAsync(dst, src, sizeof(double) * cnt, hipMemcpyDeviceToHost, s);
     return e == hipSuccess ? hipStreamSynchronize(s) : e;
   };
-  // F and <O>: written by every S v pass (here with v = 0 into the scratch p)
-  hipError_t e = launch_fill(q, (size_t)n, 0.0, s);
-  if (e == hipSuccess) e = matvec(q, p);
-  if (e == hipSuccess) e = launch_cg(kCgInit, n, x, r, p, q, F, sc, 0, shift, s);
-  if (e == hipSuccess) e = launch_cg(kCgDotRR, n, x, r, p, q, F, sc, 0, shift, s);
+  hipError_t e = timed(h, PEPS_K_SR, s,
+                       [&] { return launch_sr_sums(h->d, h->t, block_id, valid, O, e_loc, B, F, O_mean, s); });
+  if (e == hipSuccess) e = launch_cg_start(n, x, r, p, F, sc, s);
   double f2 = 0.0, rr = 0.0;
   if (e == hipSuccess) e = host(sc, &f2, 1);
   rr = f2;
   int k = 0;
   while (e == hipSuccess && f2 > 0.0 && k < max_iter && rr > rtol * rtol * f2) {
-    e = matvec(p, q);
-    if (e == hipSuccess) e = launch_cg(kCgShift, n, x, r, p, q, F, sc, k, shift, s);
-    if (e == hipSuccess) e = launch_cg(kCgDotPQ, n, x, r, p, q, F, sc, k, shift, s);
-    if (e == hipSuccess) e = launch_cg(kCgStep, n, x, r, p, q, F, sc, k, shift, s);
-    if (e == hipSuccess) e = launch_cg(kCgDotRR, n, x, r, p, q, F, sc, k + 1, shift, s);
-    double two[2] = {0.0, 0.0};  // p.q, then r.r after the step
-    if (e == hipSuccess) e = host(sc + 2 * k + 1, two, 2);
-    if (e != hipSuccess || !(two[0] > 0.0)) break;  // breakdown: x and r were left unchanged
-    rr = two[1];
+    e = timed(h, PEPS_K_SR, s,
+              [&] { return launch_sr_matvec(h->d, h->t, block_id, valid, O, B, O_mean, p, ov, q, s); });
+    if (e == hipSuccess) e = launch_cg_iteration(n, x, r, p, q, sc, k, shift, s);
+    double got[3] = {0.0, 0.0, 0.0};  // r.r by parity, p.q
+    if (e == hipSuccess) e = host(sc, got, 3);
+    if (e != hipSuccess || !(got[2] > 0.0)) break;  // breakdown: x and r were left unchanged
     ++k;
-    if (rr <= rtol * rtol * f2) break;
-    e = launch_cg(kCgDir, n, x, r, p, q, F, sc, k - 1, shift, s);
+    rr = got[k & 1];
   }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (iterations) *iterations = k;

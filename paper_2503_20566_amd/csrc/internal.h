@@ -219,19 +219,25 @@ hipError_t launch_adj_row(const Dims& d, const DeviceTables& t, int y, const dou
 hipError_t launch_vjp(const Dims& d, const DeviceTables& t, const int32_t* block_id,
                       const uint8_t* valid, const double* w, const double* O, int B, double* vjp,
                       hipStream_t s);
-// Conjugate-gradient pieces of sr_solve: vector steps and the fixed-order dot products (r.r into
-// sc[2k], p.q into sc[2k+1]).
-enum { kCgInit = 0, kCgShift = 1, kCgStep = 2, kCgDir = 3, kCgDotRR = 4, kCgDotPQ = 5 };
 constexpr int kMaxCgIter = 10000;
 hipError_t launch_sr_rows(const Dims& d, const DeviceTables& t, int64_t n_params, const int32_t* block_id,
                           const uint8_t* valid, const double* O, const double* omean, int B, int64_t row0,
                           int64_t nrows, double* S, hipStream_t s);
-hipError_t launch_cg(int op, int64_t n, double* x, double* r, double* p, double* q, const double* F,
-                     double* sc, int k, double shift, hipStream_t s);
-hipError_t launch_sr(const Dims& d, const DeviceTables& t, int64_t n_params, const int32_t* block_id,
-                     const uint8_t* valid, const double* O, const double* e_loc, int B, int mode,
-                     const double* v, double* F, double* omean, double* S_or_Sv, double* ov,
-                     double* omv, hipStream_t s);
+// F and <O> of a batch; S v = <O (O v)> - <O> (<O> . v) with that <O> (ov: double [B] scratch); dense S
+hipError_t launch_sr_sums(const Dims& d, const DeviceTables& t, const int32_t* block_id, const uint8_t* valid,
+                          const double* O, const double* e_loc, int B, double* F, double* omean, hipStream_t s);
+hipError_t launch_sr_matvec(const Dims& d, const DeviceTables& t, const int32_t* block_id, const uint8_t* valid,
+                            const double* O, int B, const double* omean, const double* v, double* ov, double* out,
+                            hipStream_t s);
+hipError_t launch_sr_dense(const Dims& d, const DeviceTables& t, int64_t n_params, const int32_t* block_id,
+                           const uint8_t* valid, const double* O, int B, const double* omean, double* S,
+                           hipStream_t s);
+// Conjugate gradients of sr_solve: x = 0, r = p = F with r.r in sc[0]; iteration k from q = S p, after
+// which sc[2] = p.q and sc[(k + 1) & 1] = r.r (unchanged vectors when p.q <= 0).  sc: kCgScalars doubles.
+constexpr int kCgScalars = 8 + 2 * 1024;
+hipError_t launch_cg_start(int64_t n, double* x, double* r, double* p, const double* F, double* sc, hipStream_t s);
+hipError_t launch_cg_iteration(int64_t n, double* x, double* r, double* p, double* q, double* sc, int k, double shift,
+                               hipStream_t s);
 hipError_t launch_close(const Dims& d, const int* bond_last, const double* proj,
                         const uint8_t* valid, int B, const double* last_row, const double* lognu,
                         double* log_abs, double* sign, hipStream_t s);

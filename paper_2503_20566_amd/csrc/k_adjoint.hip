@@ -10,8 +10,7 @@
 //     k_adj_qr  : left-to-right QR sweep in reverse (sites L-1 .. 0): QR backward and the row
 //                 application backward, giving dlnPsi/dD_{y-1} and row y's O.
 //   k_adj_row0  : row 0 is D_0 itself.
-//   k_vjp       : sum_b w_b O_b scattered into the parameter layout, per site in a fixed sample
-//                 order (deterministic, no atomics).
+// The vjp sum_b w_b O_b in the parameter layout is formed with the SR sums (k_sr.hip).
 //
 // Backward formulas used (derived from the first-order perturbation of each factorisation):
 //   * truncated SVD Theta = U S V^T (thin, p = min(m, n) triplets, the first k kept; gU, gS, gV
@@ -647,30 +646,6 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// vjp[theta] = sum_b w_b O_b: one workgroup per site, samples summed in index order.
-// ---------------------------------------------------------------------------------------------
-__global__ void k_vjp(Dims d, const int64_t* __restrict__ site_offset, const int32_t* __restrict__ block_id,
-                      const uint8_t* __restrict__ valid, const double* __restrict__ w,
-                      const double* __restrict__ O, int B, double* __restrict__ vjp) {
-  const int s = blockIdx.x;
-  const int L = d.L, Dk = d.Dk, N = d.N;
-  const int x = s % L, y = s / L;
-  const int np = (x > 0) + (x < L - 1) + (y > 0) + (y < L - 1);
-  int bs = 1, nb = 1;
-  for (int i = 0; i < np; ++i) bs *= Dk;
-  for (int i = 0; i < np - 1; ++i) nb *= N;
-  for (int ent = threadIdx.x; ent < nb * bs; ent += blockDim.x) {
-    const int blk = ent / bs, e = ent % bs;
-    double acc = 0.0;
-    for (int bb = 0; bb < B; ++bb) {
-      if (!valid[bb] || block_id[(size_t)bb * d.n_sites + s] != blk) continue;
-      acc += (w ? w[bb] : 1.0) * O[((size_t)bb * d.n_sites + s) * d.P4 + e];
-    }
-    vjp[site_offset[s] + ent] = acc;
-  }
-}
-
 __global__ void k_fill(double* __restrict__ p, size_t n, double v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
     p[i] = v;
@@ -729,14 +704,6 @@ hipError_t launch_adj_row(const Dims& d, const DeviceTables& t, int y, const dou
     GIPEPS_ADJ(32, 1)
   }
 #undef GIPEPS_ADJ
-  return hipGetLastError();
-}
-
-hipError_t launch_vjp(const Dims& d, const DeviceTables& t, const int32_t* block_id,
-                      const uint8_t* valid, const double* w, const double* O, int B, double* vjp,
-                      hipStream_t s) {
-  hipLaunchKernelGGL(k_vjp, dim3(d.n_sites), dim3(256), 0, s, d, t.site_offset, block_id, valid, w, O,
-                     B, vjp);
   return hipGetLastError();
 }
 

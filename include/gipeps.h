@@ -399,8 +399,8 @@ int peps_eloc_scale(peps_handle* h, int32_t B, const void* ws, size_t ws_bytes, 
  *                 PEPS_PRECOND_SORTED_QR
  *   precond_min   a cut is preconditioned when Theta is wide or square and its smaller dimension is
  *                 at least this (2 .. 1024)
- *   small_waves   waves per SIMD the kernels for chi * Dk <= 32 are compiled for: 2 (up to 256
- *                 registers, one workgroup per CU) or 4 (128 registers and spills, two per CU)
+ *   small_waves   2 or 4, kept for callers that set it: the kernels of each bond size are compiled
+ *                 for the waves per SIMD that their matrices in LDS leave room for
  * peps_create sets 8, SORTED_QR, QR_T, 16, 2 (the fastest at Z3 16 x 16, chi = 36). */
 enum { PEPS_PRECOND_NONE = 0, PEPS_PRECOND_QR_T = 1, PEPS_PRECOND_SORTED_QR = 2 };
 typedef struct {

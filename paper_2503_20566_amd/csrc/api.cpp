@@ -706,7 +706,7 @@ int peps_metropolis_strip(peps_handle* h, const double* theta, uint64_t seed, ui
     if (r != hipSuccess) return r;
     if (y == 0) return launch_row0_to_mps(d, proj, valid, B, down, s);
     r = launch_row_sweep(d, h->t, y, proj, valid, B, down + (size_t)(y - 1) * rs, down + (size_t)y * rs, qscr,
-                         lognu, nullptr, s, /*up=*/false, status, wbig);
+                         lognu, nullptr, s, /*up=*/true, status, wbig);
     return r == hipSuccess ? launch_var_refine(d, h->t, y, proj, valid, B, down + (size_t)(y - 1) * rs,
                                                down + (size_t)y * rs, (double*)(base + w.venv), lognu, s)
                            : r;

@@ -146,8 +146,8 @@ hipError_t launch_project(const Dims& d, const DeviceTables& t, const double* th
                           uint8_t* valid, hipStream_t s);
 hipError_t launch_row0_to_mps(const Dims& d, const double* proj, const uint8_t* valid, int B,
                               double* out_row, hipStream_t s);
-// up: an up sweep (mirrored lattice; its factorisations are never reversed), preconditioned with
-// d.up_precond, else d.down_precond (see peps_tuning)
+// up: a sweep that is never reversed (the up sweeps, and every sweep of the strip sampler),
+// preconditioned with d.up_precond; else one that peps_logderiv may reverse, with d.down_precond
 // status (uint32 [B] or null): bit PEPS_FLAG_SVD_NOCONV is OR-ed in for a sample whose Jacobi
 // stopped at the sweep limit without converging
 hipError_t launch_row_sweep(const Dims& d, const DeviceTables& t, int y, const double* proj,
@@ -182,6 +182,33 @@ struct RaggedRows {
 // precondition settings: taken from `tune` (the first group's handle)
 hipError_t launch_row_sweep_ragged(const RaggedRows& r, int total_blocks, int y, int Dk, int maxN,
                                    const Dims& tune, hipStream_t s);
+// Instantiation of the row sweep and its adjoint for fused bonds up to maxN (0: none)
+inline int row_class(int maxN, int Dk) {
+  if (Dk == 1 || maxN <= 16) return 16;  // D_k = 1: every bond has dimension 1
+  return maxN <= 32 ? 32 : maxN <= 48 ? 48 : maxN <= kMaxN ? kMaxN : maxN <= kMaxNBig ? kMaxNBig : 0;
+}
+// Arguments of one row launch (host side): one lattice, or the groups of a ragged batch (ragged set)
+struct RowArgs {
+  int blocks, y, pmode, pthr, lanes;
+  bool mixed;
+  const RaggedRows* ragged;
+  const Dims* d;
+  const int* bond;
+  const int* qrk;
+  const double* proj;
+  const uint8_t* valid;
+  const double* prev_row;
+  double* out_row;
+  double* qscr;
+  size_t qslot;  // doubles per (sample, site) Q-factor slot
+  double* lognu;
+  double* tape;
+  size_t tslot;  // doubles per (sample, site) tape slot
+  uint32_t* status;
+  double* wbig;
+};
+template <int MAXN, int DK>
+hipError_t launch_row_class(const RowArgs& a, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
 // variational compression of row y's boundary (out_row, in place) against the exact product of row
 // y with prev_row; a no-op when d.var_sweeps == 0

@@ -35,7 +35,11 @@ namespace gipeps {
 
 namespace {
 
-constexpr int kT = 512;
+// Threads of the adjoint kernels of each class: as the row sweep's, fewer at small bonds so that several
+// samples share a compute unit (Z2 16 x 16, chi = 16, 1024 samples: k_adj_qr 1.63 -> 1.03 ms per row, k_adj_svd
+// 0.45 -> 0.36 ms).
+template <int MAXN>
+constexpr int adj_threads() { return MAXN == 16 ? 128 : MAXN == 32 ? 256 : 512; }
 
 // Accessors of one taped SVD (site c >= 1): U (m x p), V (n x p), sorted singular values.
 template <int MAXN>
@@ -50,7 +54,7 @@ struct SvdTape {
 };
 
 // Stage the singular values of a taped SVD into LDS.
-template <int MAXN>
+template <int MAXN, int kT>
 __device__ SvdTape<MAXN> load_svd(const double* slot, int m, int n, double* sSig) {
   using TS = TapeSlot<MAXN>;
   SvdTape<MAXN> t;
@@ -169,13 +173,13 @@ __global__ void k_adj_row0(Dims d, const uint8_t* __restrict__ valid, const doub
 // Normalisation and SVD sweep in reverse for row y.
 // ---------------------------------------------------------------------------------------------
 template <int MAXN, int DK>
-__global__ void __launch_bounds__(kT)
+__global__ void __launch_bounds__(adj_threads<MAXN>())
 k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_all, int y,
           const uint8_t* __restrict__ valid, const double* __restrict__ cur_row,
           const double* __restrict__ tape, const double* __restrict__ qscr,
           const double* __restrict__ psibar_in, double* __restrict__ qbar, double* __restrict__ xbar,
-          double* __restrict__ wbig) {
-  constexpr int MAXM = MAXN * DK;
+          size_t qslot, size_t tslot, double* __restrict__ wbig) {
+  constexpr int MAXM = MAXN * DK, kT = adj_threads<MAXN>();
   constexpr int KD = MAXN / DK;  // largest kept bond
   // large bonds: three of the working matrices in the sample's global slot (wbig), the core /
   // Theta-bar and the staging in LDS
@@ -204,9 +208,9 @@ k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_
   const int L = d.L, Dk = DK;
   const int* bnew = bond_all + (size_t)y * (L + 1);
   const int* qrk = qrk_all + (size_t)y * L;
-  const double* tp = tape + (size_t)b * L * TS::size;
-  const double* qs = qscr + (size_t)b * L * (MAXM * MAXN);
-  double* qb = qbar + (size_t)b * L * (MAXM * MAXN);
+  const double* tp = tape + (size_t)b * L * tslot;
+  const double* qs = qscr + (size_t)b * L * qslot;
+  double* qb = qbar + (size_t)b * L * qslot;
   const double* psi = cur_row + (size_t)b * d.row_stride;
   const double* pbar = psibar_in + (size_t)b * d.row_stride;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -220,7 +224,7 @@ k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_
     const double dot = block_sum(part, sRed);
     for (int i = threadIdx.x; i < n0; i += kT) sC[i] = (pbar[i] + psi[i] * (1.0 - dot)) / nu;
     const int m1 = qrk[0], n1 = Dk * ((L - 1 == 1) ? 1 : bnew[2]);
-    SvdTape<MAXN> t1 = load_svd<MAXN>(tp + (size_t)1 * TS::size, m1, n1, sSig);
+    SvdTape<MAXN> t1 = load_svd<MAXN, kT>(tp + (size_t)1 * tslot, m1, n1, sSig);
     // Qbar_0[(u)][t] = sum_j Thetabar_0[u][j] G_1[t][j];  Gbar_1[t][j] = sum_u Q_0[u][t] Thetabar_0[u][j]
     for (int idx = threadIdx.x; idx < Dk * r0; idx += kT) {
       const int t = idx / Dk, u = idx % Dk;
@@ -243,7 +247,7 @@ k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_
     const int chin = (c == L - 1) ? 1 : bnew[c + 1];
     const int n = Dk * chin;
     const int kk = bnew[c];
-    SvdTape<MAXN> t = load_svd<MAXN>(tp + (size_t)c * TS::size, m, n, sSig);
+    SvdTape<MAXN> t = load_svd<MAXN, kT>(tp + (size_t)c * tslot, m, n, sSig);
     const int p = t.nc;  // = min(m, n)
     // gS[a] = sum_i U[i][a] Gbar[i][a];  gV[col][a] = psibar_c[a][col]
     for (int a = wave; a < kk; a += kT / 64) {
@@ -314,9 +318,9 @@ k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_
       // Theta_c[i][(u,j)] = sum_t Q_c[(i,u)][t] G_{c+1}[t][j]
       const int rc = qrk[c], mq = m * Dk;
       const int m2 = rc, n2 = Dk * ((c + 1 == L - 1) ? 1 : bnew[c + 2]);
-      SvdTape<MAXN> t2 = load_svd<MAXN>(tp + (size_t)(c + 1) * TS::size, m2, n2, sSig);
-      const double* Qc = qs + (size_t)c * (MAXM * MAXN);
-      double* Qb = qb + (size_t)c * (MAXM * MAXN);
+      SvdTape<MAXN> t2 = load_svd<MAXN, kT>(tp + (size_t)(c + 1) * tslot, m2, n2, sSig);
+      const double* Qc = qs + (size_t)c * qslot;
+      double* Qb = qb + (size_t)c * qslot;
       auto th = [&](int row, int j) { return sC[(row / Dk) * n + (row % Dk) * chin + j]; };
       mfma_gemm_staged<QT, KCH, SPT, false>(
           mq, rc, chin, [&](int tt, int j) { return t2.G(tt, j); }, th, sBuf,
@@ -336,14 +340,14 @@ k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_
 // QR sweep and row application in reverse for row y: psibar_{y-1} and O of row y.
 // ---------------------------------------------------------------------------------------------
 template <int MAXN, int DK>
-__global__ void __launch_bounds__(kT)
+__global__ void __launch_bounds__(adj_threads<MAXN>())
 k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_all, int y,
          const double* __restrict__ proj, const uint8_t* __restrict__ valid,
          const double* __restrict__ prev_row, const double* __restrict__ qscr,
          const double* __restrict__ tape, const double* __restrict__ qbar,
          const double* __restrict__ xbar, double* __restrict__ psibar_out, double* __restrict__ O,
-         double* __restrict__ wbig) {
-  constexpr int MAXM = MAXN * DK;
+         size_t qslot, size_t tslot, double* __restrict__ wbig) {
+  constexpr int MAXM = MAXN * DK, kT = adj_threads<MAXN>();
   // 16 x 16 matrix-core tiles per wave of the products with up to MAXM x MAXN outputs
   constexpr int QT = ((MAXM + 15) / 16 * ((MAXN + 15) / 16) + kT / 64 - 1) / (kT / 64);
   // large bonds: Xbar and Z in the sample's global slot (wbig), Rbar in LDS, B read from the
@@ -371,9 +375,9 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
   const int L = d.L, Dk = DK;
   const int* bprev = bond_all + (size_t)(y - 1) * (L + 1);
   const int* qrk = qrk_all + (size_t)y * L;
-  const double* tp = tape + (size_t)b * L * TS::size;
-  const double* qs = qscr + (size_t)b * L * (MAXM * MAXN);
-  const double* qb = qbar + (size_t)b * L * (MAXM * MAXN);
+  const double* tp = tape + (size_t)b * L * tslot;
+  const double* qs = qscr + (size_t)b * L * qslot;
+  const double* qb = qbar + (size_t)b * L * qslot;
   const double* prev = prev_row + (size_t)b * d.row_stride;
   double* pout = psibar_out + (size_t)b * d.row_stride;
   const double* pb = proj + ((size_t)b * d.n_sites + (size_t)y * L) * d.P4;
@@ -399,7 +403,7 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
     for (int i = threadIdx.x; i < dl * dr * Dk * Dk; i += kT) sT[i] = pb[(size_t)c * d.P4 + i];
     // R_{c-1} (r x mc, ld MAXN) staged in sRb until the products that read it are done
     if (c >= 1) {
-      const double* Rt = tp + (size_t)(c - 1) * TS::size + TS::R;
+      const double* Rt = tp + (size_t)(c - 1) * tslot + TS::R;
       if constexpr (BIG) {
         for (int idx = threadIdx.x; idx < mc * MAXN; idx += kT) sRb[idx] = (idx % MAXN < r) ? Rt[idx] : 0.0;
       } else {
@@ -541,9 +545,9 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
     // ---- QR backward of X_{c-1} = Q R (m2 x n2, k2 = min) -> Xbar_{c-1} in sXb (ld m2)
     const int r2 = (c - 1 == 0) ? 1 : qrk[c - 2];
     const int m2 = r2 * Dk, n2 = mc, k2 = qrk[c - 1];
-    const double* Q = qs + (size_t)(c - 1) * (MAXM * MAXN);    // m2 x k2, ld m2
-    const double* Qb = qb + (size_t)(c - 1) * (MAXM * MAXN);   // m2 x k2, ld m2
-    const double* Rq = tp + (size_t)(c - 1) * TS::size + TS::R;  // k2 x n2, ld MAXN
+    const double* Q = qs + (size_t)(c - 1) * qslot;    // m2 x k2, ld m2
+    const double* Qb = qb + (size_t)(c - 1) * qslot;   // m2 x k2, ld m2
+    const double* Rq = tp + (size_t)(c - 1) * tslot + TS::R;  // k2 x n2, ld MAXN
     auto RQ = [&](int i, int j) -> double { return Rq[(size_t)j * MAXN + i]; };
     // Qbar' = Qbar + Q R2 R2bar^T (cols < k2) and Xbar[:, k2:] = Q R2bar; all loads of a thread
     // are issued before its stores
@@ -688,20 +692,26 @@ hipError_t launch_adj_row(const Dims& d, const DeviceTables& t, int y, const dou
                           double* O, hipStream_t s, double* wbig) {
   if (B == 0) return hipSuccess;
   if (d.maxN > kMaxN && (d.Dk != 2 || d.maxN > kMaxNBig || !wbig)) return hipErrorInvalidValue;
-#define GIPEPS_ADJ(MN, DKV)                                                                          \
-  hipLaunchKernelGGL((k_adj_svd<MN, DKV>), dim3(B), dim3(kT), 0, s, d, t.bond, t.qrk, y, valid,      \
-                     cur_row, tape, qscr, psibar_in, qbar, xbar, wbig);                              \
-  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;                                 \
-  hipLaunchKernelGGL((k_adj_qr<MN, DKV>), dim3(B), dim3(kT), 0, s, d, t.bond, t.qrk, y, proj, valid, \
-                     prev_row, qscr, tape, qbar, xbar, psibar_out, O, wbig);
-  if (d.Dk == 2 && d.maxN <= 32) {
-    GIPEPS_ADJ(32, 2)
-  } else if (d.Dk == 2 && d.maxN <= kMaxN) {
-    GIPEPS_ADJ(72, 2)
-  } else if (d.Dk == 2) {
-    GIPEPS_ADJ(kMaxNBig, 2)
-  } else {
-    GIPEPS_ADJ(32, 1)
+  const size_t qslot = qslot_doubles(d), tslot = tape_slot_doubles(d);
+#define GIPEPS_ADJ(MN, DKV)                                                                                      \
+  hipLaunchKernelGGL((k_adj_svd<MN, DKV>), dim3(B), dim3(adj_threads<MN>()), 0, s, d, t.bond, t.qrk, y, valid,    \
+                     cur_row, tape, qscr, psibar_in, qbar, xbar, qslot, tslot, wbig);                            \
+  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;                                             \
+  hipLaunchKernelGGL((k_adj_qr<MN, DKV>), dim3(B), dim3(adj_threads<MN>()), 0, s, d, t.bond, t.qrk, y, proj, valid, \
+                     prev_row, qscr, tape, qbar, xbar, psibar_out, O, qslot, tslot, wbig);
+  switch (row_class(d.maxN, d.Dk)) {
+    case 16:
+      if (d.Dk == 1) {
+        GIPEPS_ADJ(16, 1)
+      } else {
+        GIPEPS_ADJ(16, 2)
+      }
+      break;
+    case 32: GIPEPS_ADJ(32, 2) break;
+    case 48: GIPEPS_ADJ(48, 2) break;
+    case 72: GIPEPS_ADJ(72, 2) break;
+    case kMaxNBig: GIPEPS_ADJ(kMaxNBig, 2) break;
+    default: return hipErrorInvalidValue;
   }
 #undef GIPEPS_ADJ
   return hipGetLastError();

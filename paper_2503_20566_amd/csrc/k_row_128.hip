@@ -1,0 +1,6 @@
+// Row sweep (row_sweep.h) for fused bonds up to 128.
+#include "row_sweep.h"
+
+namespace gipeps {
+template hipError_t launch_row_class<kMaxNBig, 2>(const RowArgs&, hipStream_t);
+}  // namespace gipeps

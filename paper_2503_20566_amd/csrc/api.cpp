@@ -803,10 +803,11 @@ int peps_local_energy(peps_handle* h, const double* theta, const uint8_t* links,
                               (double*)(base + w.venv), uplognu, s);
       return r;
     });
-  for (int py = 0; py <= d.L - 2 && e == hipSuccess; ++py)
+  const int per = strips_per_launch(d);
+  for (int py = 0; py <= d.L - 2 && e == hipSuccess; py += per)
     e = timed(h, PEPS_K_STRIP, s, [&] {
-      return launch_strip(d, py, h->t, proj, theta, links, valid, B, down, up, h->t.plaq, h->hop, strip,
-                          part, pabs, s, wbig);
+      return launch_strip(d, py, std::min(per, d.L - 1 - py), h->t, proj, theta, links, valid, B, down, up, h->t.plaq,
+                          h->hop, strip, part, pabs, s, wbig);
     });
   if (e == hipSuccess)
     e = launch_eloc_final(d, links, valid, B, h->t.elec, h->mass, part, pabs, e_loc, escale, s);

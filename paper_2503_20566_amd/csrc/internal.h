@@ -219,10 +219,12 @@ size_t tape_slot_doubles(const Dims& d);  // doubles per (sample, site) of the r
 size_t strip_scratch_doubles(const Dims& d);
 hipError_t launch_mirror_proj(const Dims& d, const double* proj, const uint8_t* valid, int B,
                               double* fproj, hipStream_t s);
-hipError_t launch_strip(const Dims& d, int py, const DeviceTables& t, const double* proj,
-                        const double* theta, const uint8_t* links, const uint8_t* valid, int B,
-                        const double* down, const double* up, const double* plaq, double hop,
-                        double* scratch, double* part, double* pabs, hipStream_t s, double* wbig = nullptr);
+// strips py .. py + strips - 1 in one launch, at most strips_per_launch of them (what the scratch holds)
+int strips_per_launch(const Dims& d);
+hipError_t launch_strip(const Dims& d, int py, int strips, const DeviceTables& t, const double* proj,
+                        const double* theta, const uint8_t* links, const uint8_t* valid, int B, const double* down,
+                        const double* up, const double* plaq, double hop, double* scratch, double* part, double* pabs,
+                        hipStream_t s, double* wbig = nullptr);
 // links_pass 0: the strip's plaquette moves; 1 (matter): its link moves
 hipError_t launch_strip_mc(const Dims& d, int py, int sweep, uint64_t seed, uint64_t stream,
                            const DeviceTables& t, const double* theta, uint8_t* links,

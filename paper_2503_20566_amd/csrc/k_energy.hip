@@ -34,15 +34,25 @@ namespace gipeps {
 
 namespace {
 
-constexpr int kT = 512;
-constexpr int kW = kT / 64;
-constexpr int kEnv = kMaxN / kMaxDk * kMaxDk * kMaxDk * (kMaxN / kMaxDk);  // chi*2*2*chi = 5184
-constexpr int kX = kEnv * kMaxDk;                                         // 10368
-constexpr int kSite = kEnv / kMaxDk;                 // chi*2*chi = 2592: one boundary site
-constexpr int kPPT = (kX / 8 + kT - 1) / kT;          // (b, a') pairs per thread in the W contractions
-// large bonds (chi <= 64 at D_k = 2): the same quantities, held in the sample's global slot
-constexpr int kEnvBig = (kMaxNBig / kMaxDk) * kMaxDk * kMaxDk * (kMaxNBig / kMaxDk);  // 16384
-constexpr int kXBig = kEnvBig * kMaxDk;                                               // 32768
+// Sizes of the strip kernels for boundary bonds up to CH (the row sweep's classes: 8, 16, 24, 36, and
+// 64, where X and the staged site live in the sample's global slot): the environment chi*2*2*chi, X (one
+// physical leg more) and one boundary site chi*2*chi, in doubles; the threads of a workgroup.  As in the
+// row sweep what counts is how many samples share a compute unit, so the LDS follows the bonds: sized for
+// 36 throughout (147 KB, one workgroup per CU), a strip of Z2 16 x 16, chi = 16, 512 chains took
+// 1.17 ms in the sampler; with 30 KB and 256 threads 0.63 ms.
+template <int CH>
+struct StripCfg {
+  static constexpr bool BIG = CH > kMaxN / kMaxDk;
+  static constexpr int ENV = CH * kMaxDk * kMaxDk * CH;
+  static constexpr int XS = ENV * kMaxDk;
+  static constexpr int SITE = ENV / kMaxDk;
+  static constexpr int NT = CH == 8 ? 128 : CH == 16 ? 256 : 512;
+  static constexpr int PPT = (XS / 8 + NT - 1) / NT;  // (b, a') pairs per thread in the W contractions
+  static_assert(!BIG || XS + SITE <= kBigSlot, "large-bond slot");
+};
+constexpr int kX = StripCfg<kMaxN / kMaxDk>::XS;       // X1 / Y1 slots that the workspace holds per column
+constexpr int kXBig = StripCfg<kMaxNBig / kMaxDk>::XS;
+constexpr int kMaxL = 64;
 
 struct Strip {
   int L, N, Dk, py, dD, dU, B;
@@ -57,6 +67,7 @@ struct Strip {
 };
 
 // W[l][l'][d][r][r'][u'] of column c from the lower (lo) and upper (hi) row blocks.
+template <int kT>
 __device__ void build_w(const Strip& S, int c, const double* lo, const double* hi, double* W) {
   const int hl = S.hl(c), hr = S.hl(c + 1), Dk = S.Dk, dD = S.dD, dU = S.dU;
   const int n = hl * hl * dD * hr * hr * dU;
@@ -84,9 +95,24 @@ struct Move {
 __device__ __forceinline__ Move plaquette_move(int px, int py, int t) { return Move{px, py, t, 0, 0, 0, 0}; }
 __device__ __forceinline__ Move hop_move(int d, int x, int y, int step) { return Move{0, 0, 0, d, x, y, step}; }
 
+// The configuration around a strip in LDS: rows py - 1 .. py + 1 of each plane (the links and occupations
+// that the strip's sites see), so that a window's blocks wait for one global read, not for two.
+struct StripLinks {
+  uint8_t* s;  // [3][3][kMaxL]
+  int py;
+  __device__ uint8_t& at(int plane, int x, int y) const { return s[(plane * 3 + (y - py + 1)) * kMaxL + x]; }
+};
+template <int kT>
+__device__ void load_links(const StripLinks& l, const uint8_t* lk, int L, int planes) {
+  for (int i = threadIdx.x; i < planes * 3 * L; i += kT) {
+    const int x = i % L, y = l.py - 1 + (i / L) % 3, plane = i / (3 * L);
+    l.at(plane, x, y) = (y >= 0 && y < L) ? lk[(size_t)plane * L * L + y * L + x] : 0;
+  }
+}
+
 // Label of link (dir, x, y) in the configuration mv leads to.
-__device__ int mlabel(const uint8_t* lk, int L, int N, int dir, int x, int y, const Move& mv) {
-  int n = lk[(size_t)dir * L * L + y * L + x];
+__device__ int mlabel(const StripLinks& lk, int N, int dir, int x, int y, const Move& mv) {
+  int n = lk.at(dir, x, y);
   const int px = mv.px, py = mv.py, t = mv.t;
   if (dir == 0 && y == py && x == px) n -= t;
   if (dir == 1 && y == py && x == px + 1) n -= t;
@@ -99,48 +125,51 @@ __device__ int mlabel(const uint8_t* lk, int L, int N, int dir, int x, int y, co
 
 // Occupation of vertex (x, y) in the configuration mv leads to (0 without matter): a hop
 // exchanges the occupations of the link's two ends.
-__device__ int mocc(const uint8_t* lk, int L, bool matter, int x, int y, const Move& mv) {
+__device__ int mocc(const StripLinks& lk, bool matter, int x, int y, const Move& mv) {
   if (!matter) return 0;
   if (mv.hstep != 0) {
     const int bx = mv.hx + (mv.hd == 0), by = mv.hy + (mv.hd == 1);
-    if (x == mv.hx && y == mv.hy) return lk[(size_t)2 * L * L + by * L + bx];
-    if (x == bx && y == by) return lk[(size_t)2 * L * L + mv.hy * L + mv.hx];
+    if (x == mv.hx && y == mv.hy) return lk.at(2, bx, by);
+    if (x == bx && y == by) return lk.at(2, mv.hx, mv.hy);
   }
-  return lk[(size_t)2 * L * L + y * L + x];
+  return lk.at(2, x, y);
 }
 
-// Gather the block of site (x, y) selected by the configuration mv leads to into dst
-// (Dk^#legs entries): p-major block index, as in the projection.
-__device__ void gather_block(const double* theta, const int64_t* site_offset, const uint8_t* lk,
-                             int L, int N, int Dk, bool matter, int x, int y, const Move& mv, double* dst) {
+// Gather the blocks (Dk^#legs entries) of the sites (x0 + c, py + r), c < cols, r < 2, that the
+// configuration mv leads to select, into dst[2 c + r]: p-major block index, as in the projection.  16 lanes
+// per block, so that all of a window's reads are in flight together.
+__device__ void gather_blocks(const double* theta, const int64_t* site_offset, const StripLinks& lk, int L, int N,
+                              int Dk, bool matter, int x0, int cols, const Move& mv, double (*dst)[16]) {
+  const int i = threadIdx.x >> 4, e = threadIdx.x & 15;
+  if (i >= 2 * cols) return;
+  const int x = x0 + (i >> 1), y = lk.py + (i & 1);
   const bool pres[4] = {x > 0, x < L - 1, y > 0, y < L - 1};
   int q[4];
-  q[0] = pres[0] ? mlabel(lk, L, N, 0, x - 1, y, mv) : 0;
-  q[1] = pres[1] ? mlabel(lk, L, N, 0, x, y, mv) : 0;
-  q[2] = pres[2] ? mlabel(lk, L, N, 1, x, y - 1, mv) : 0;
-  q[3] = pres[3] ? mlabel(lk, L, N, 1, x, y, mv) : 0;
+  q[0] = pres[0] ? mlabel(lk, N, 0, x - 1, y, mv) : 0;
+  q[1] = pres[1] ? mlabel(lk, N, 0, x, y, mv) : 0;
+  q[2] = pres[2] ? mlabel(lk, N, 1, x, y - 1, mv) : 0;
+  q[3] = pres[3] ? mlabel(lk, N, 1, x, y, mv) : 0;
   int npres = 0;
-  for (int i = 0; i < 4; ++i) npres += pres[i];
+  for (int j = 0; j < 4; ++j) npres += pres[j];
   int idx = 0, seen = 0, per_occ = 1;
-  for (int i = 0; i < 4; ++i) {
-    if (!pres[i]) continue;
+  for (int j = 0; j < 4; ++j) {
+    if (!pres[j]) continue;
     if (seen < npres - 1) {
-      idx = idx * N + q[i];
+      idx = idx * N + q[j];
       per_occ *= N;
     }
     ++seen;
   }
-  idx += mocc(lk, L, matter, x, y, mv) * per_occ;
+  idx += mocc(lk, matter, x, y, mv) * per_occ;
   int bsize = 1;
-  for (int i = 0; i < npres; ++i) bsize *= Dk;
-  const double* src = theta + site_offset[y * L + x] + (int64_t)idx * bsize;
-  for (int i = threadIdx.x; i < bsize; i += kT) dst[i] = src[i];
+  for (int j = 0; j < npres; ++j) bsize *= Dk;
+  if (e < bsize) dst[i][e] = theta[site_offset[y * L + x] + (int64_t)idx * bsize + e];
 }
 
 // Boundary site (rows x cols, row-major, n <= SITE entries) from global memory into LDS (or the
 // sample's global slot); a trivial boundary (src == nullptr) is the 1 x 1 tensor 1.  All loads of
 // a thread precede its stores.
-template <int SITE = kSite>
+template <int SITE, int kT>
 __device__ void stage_site(double* dst, const double* src, int n) {
   constexpr int SPT = (SITE + kT - 1) / kT;
   if (!src) {
@@ -163,7 +192,7 @@ __device__ void stage_site(double* dst, const double* src, int n) {
 // X3[(b,a')][o] = sum_i X1[(l,l',b,d,a')] W[i][o] over the cU*cDn pairs (b, a'), i = (l,l',d) < ni,
 // o = (r,r',u') < no (both <= 8).  Each pair's inputs are read once and give all its outputs.
 // In place (src == dst) every thread reads before the barrier and writes after it.
-template <bool INPLACE, int PPT = kPPT>
+template <bool INPLACE, int PPT, int kT>
 __device__ void contract_left(const double* X1, double* dst, const double* W, int cU, int cDn, int dD,
                               int ni, int no) {
   double out[PPT][8];
@@ -203,7 +232,7 @@ __device__ void contract_left(const double* X1, double* dst, const double* W, in
 
 // Y3[(a',l,l',b,d)] = sum_o Y1[(a',r,r',b,u')] W[i][o] over the cDn*cU pairs (a', b), same index
 // conventions as contract_left.
-template <bool INPLACE, int PPT = kPPT>
+template <bool INPLACE, int PPT, int kT>
 __device__ void contract_right(const double* Y1, double* dst, const double* W, int cU, int cDn, int dU,
                                int dD, int ni, int no) {
   double out[PPT][8];
@@ -270,28 +299,31 @@ __global__ void k_mirror_proj(Dims d, const double* __restrict__ proj,
   }
 }
 
-// BIG: fused bonds above 72 (chi <= 64): X and the staged site in the sample's global slot (wbig)
-// instead of LDS, the environment E still in LDS, X1 / Y1 slots of kXBig doubles
-template <bool BIG>
-__global__ void __launch_bounds__(kT)
-k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restrict__ proj,
+// CH: largest boundary bond; above 36 X and the staged site in the sample's global slot (wbig) instead of
+// LDS, the environment still in LDS.  Workgroup (b, k): sample b, strip py0 + k; its X1 / Y1 slots of XS
+// doubles at part k of the scratch, which is sized for the bonds of 36, so that several strips of
+// smaller bonds run in one launch (a batch that does not fill the chip then waits for one strip's latency,
+// not for each: Z3 6 x 6, chi = 6, 33 samples, five launches of 222 us -> one of 160).
+template <int CH>
+__global__ void __launch_bounds__(StripCfg<CH>::NT)
+k_strip(Dims d, int py0, const int* __restrict__ bond_all, const double* __restrict__ proj,
         const double* __restrict__ theta, const int64_t* __restrict__ site_offset,
         const uint8_t* __restrict__ links, const uint8_t* __restrict__ valid,
         const double* __restrict__ down, const double* __restrict__ up,
         const double* __restrict__ plaq, double hop, double* __restrict__ scratch,
         double* __restrict__ part, double* __restrict__ pabs, double* __restrict__ wbig) {
-  constexpr int ENV = BIG ? kEnvBig : kEnv;
-  constexpr int XS = BIG ? kXBig : kX;
-  constexpr int SITE = ENV / kMaxDk;
-  constexpr int PPT = (XS / 8 + kT - 1) / kT;
-  static_assert(!BIG || XS + SITE <= kBigSlot, "large-bond slot");
+  using Cfg = StripCfg<CH>;
+  constexpr bool BIG = Cfg::BIG;
+  constexpr int ENV = Cfg::ENV, XS = Cfg::XS, SITE = Cfg::SITE, PPT = Cfg::PPT, kT = Cfg::NT;
   __shared__ double lE[ENV];  // the environment stays in LDS (128 KB at the large size)
   __shared__ double lX[BIG ? 1 : XS];
   __shared__ double sW[64];
   __shared__ double sW2[64];
   __shared__ double lS[BIG ? 1 : SITE];  // staged boundary site (D or U) of the product at hand
   __shared__ double sTb[4][16];
-  __shared__ double sRed[kW];
+  __shared__ double sRed[kT / 64];
+  __shared__ uint8_t sLk[9 * kMaxL];
+  const int py = py0 + (int)blockIdx.y;
   const int b = blockIdx.x;
   if (!valid[b]) return;
   double* const sE = lE;
@@ -310,10 +342,11 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
   S.Urow = S.bU ? up + (size_t)(L - 3 - py) * rs + (size_t)b * d.row_stride : nullptr;
   const double* plo = proj + ((size_t)b * d.n_sites + (size_t)py * L) * d.P4;
   const double* phi = proj + ((size_t)b * d.n_sites + (size_t)(py + 1) * L) * d.P4;
-  const uint8_t* lk = links + (size_t)b * d.planes * L * L;
+  const StripLinks lk{sLk, py};
+  load_links<kT>(lk, links + (size_t)b * d.planes * L * L, L, d.planes);
   const bool matter = d.matter != 0;
-  // per-sample scratch: X1_c and Y1_c, L slots of XS each
-  double* gX1 = scratch + (size_t)b * ((size_t)2 * L * XS);
+  // scratch of this sample and strip: X1_c and Y1_c, L slots of XS each
+  double* gX1 = scratch + ((size_t)blockIdx.y * gridDim.x + b) * ((size_t)2 * L * XS);
   double* gY1 = gX1 + (size_t)L * XS;
   const int dD = S.dD, dU = S.dU;
 
@@ -323,9 +356,9 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
   for (int c = 0; c < L; ++c) {
     const int hl = S.hl(c), hr = S.hl(c + 1);
     const int cD = S.chiD(c), cDn = S.chiD(c + 1), cU = S.chiU(c), cUn = S.chiU(c + 1);
-    build_w(S, c, plo + (size_t)c * d.P4, phi + (size_t)c * d.P4, sW);
+    build_w<kT>(S, c, plo + (size_t)c * d.P4, phi + (size_t)c * d.P4, sW);
     // X1[(l,l',b)][(d,a')] = sum_a E[a][(l,l',b)] D[a][(d,a')]
-    stage_site<SITE>(sS, S.Drow ? S.Drow + (size_t)c * S.site_stride : nullptr, cD * dD * cDn);
+    stage_site<SITE, kT>(sS, S.Drow ? S.Drow + (size_t)c * S.site_stride : nullptr, cD * dD * cDn);
     __syncthreads();
     {
       const int rows = hl * hl * cU, cols = dD * cDn;
@@ -339,8 +372,8 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
     }
     __syncthreads();
     // X3[b][a'][r][r'][u'] = sum_{l,l',d} X1[l][l'][b][d][a'] W[l][l'][d][r][r'][u'] (in place)
-    contract_left<true, PPT>(sX, sX, sW, cU, cDn, dD, hl * hl * dD, hr * hr * dU);
-    stage_site<SITE>(sS, S.Urow ? S.Urow + (size_t)c * S.site_stride : nullptr, cU * dU * cUn);
+    contract_left<true, PPT, kT>(sX, sX, sW, cU, cDn, dD, hl * hl * dD, hr * hr * dU);
+    stage_site<SITE, kT>(sS, S.Urow ? S.Urow + (size_t)c * S.site_stride : nullptr, cU * dU * cUn);
     __syncthreads();
     // E'[(a',r,r')][b'] = sum_{(b,u')} X3[b][(a',r,r')][u'] U[(b,u')][b']
     {
@@ -361,9 +394,9 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
   for (int c = L - 1; c >= 0; --c) {
     const int hl = S.hl(c), hr = S.hl(c + 1);
     const int cD = S.chiD(c), cDn = S.chiD(c + 1), cU = S.chiU(c), cUn = S.chiU(c + 1);
-    build_w(S, c, plo + (size_t)c * d.P4, phi + (size_t)c * d.P4, sW);
+    build_w<kT>(S, c, plo + (size_t)c * d.P4, phi + (size_t)c * d.P4, sW);
     // Y1[(a',r,r')][(b,u')] = sum_{b'} F[(a',r,r')][b'] U[(b,u')][b']
-    stage_site<SITE>(sS, S.Urow ? S.Urow + (size_t)c * S.site_stride : nullptr, cU * dU * cUn);
+    stage_site<SITE, kT>(sS, S.Urow ? S.Urow + (size_t)c * S.site_stride : nullptr, cU * dU * cUn);
     __syncthreads();
     {
       const int rows = cDn * hr * hr, cols = cU * dU;
@@ -377,8 +410,8 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
     }
     __syncthreads();
     // Y3[a'][l][l'][b][d] = sum_{r,r',u'} Y1[a'][r][r'][b][u'] W[l][l'][d][r][r'][u'] (in place)
-    contract_right<true, PPT>(sX, sX, sW, cU, cDn, dU, dD, hl * hl * dD, hr * hr * dU);
-    stage_site<SITE>(sS, S.Drow ? S.Drow + (size_t)c * S.site_stride : nullptr, cD * dD * cDn);
+    contract_right<true, PPT, kT>(sX, sX, sW, cU, cDn, dU, dD, hl * hl * dD, hr * hr * dU);
+    stage_site<SITE, kT>(sS, S.Drow ? S.Drow + (size_t)c * S.site_stride : nullptr, cD * dD * cDn);
     __syncthreads();
     // F[a][(l,l',b)] = sum_{(a',d)} D[a][d][a'] Y3[a'][(l,l',b)][d]
     {
@@ -397,20 +430,17 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
   // the right half G_R = (Y1_{px+1} . W'_{px+1}) . D_{px+1}
   auto window_num = [&](const Move& mv, int px) -> double {
     const int c0 = px, c1 = px + 1;
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, c0, py, mv, sTb[0]);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, c0, py + 1, mv, sTb[1]);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, c1, py, mv, sTb[2]);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, c1, py + 1, mv, sTb[3]);
+    gather_blocks(theta, site_offset, lk, L, N, Dk, matter, px, 2, mv, sTb);
     __syncthreads();
-    build_w(S, c0, sTb[0], sTb[1], sW);
-    build_w(S, c1, sTb[2], sTb[3], sW2);
+    build_w<kT>(S, c0, sTb[0], sTb[1], sW);
+    build_w<kT>(S, c1, sTb[2], sTb[3], sW2);
     __syncthreads();
     {
       const int hl = S.hl(c0), hr = S.hl(c0 + 1);
       const int cU = S.chiU(c0), cDn = S.chiD(c0 + 1), cUn = S.chiU(c0 + 1);
       const double* X1 = gX1 + (size_t)c0 * XS;
-      contract_left<false, PPT>(X1, sX, sW, cU, cDn, dD, hl * hl * dD, hr * hr * dU);
-      stage_site<SITE>(sS, S.Urow ? S.Urow + (size_t)c0 * S.site_stride : nullptr, cU * dU * cUn);
+      contract_left<false, PPT, kT>(X1, sX, sW, cU, cDn, dD, hl * hl * dD, hr * hr * dU);
+      stage_site<SITE, kT>(sS, S.Urow ? S.Urow + (size_t)c0 * S.site_stride : nullptr, cU * dU * cUn);
       __syncthreads();
       const int rows = cDn * hr * hr, K = cU * dU;
       mfma_gemm(rows, cUn, K,
@@ -424,8 +454,8 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
       const int hl = S.hl(c1), hr = S.hl(c1 + 1);
       const int cD = S.chiD(c1), cDn = S.chiD(c1 + 1), cU = S.chiU(c1);
       const double* Y1 = gY1 + (size_t)c1 * XS;
-      contract_right<false, PPT>(Y1, sX, sW2, cU, cDn, dU, dD, hl * hl * dD, hr * hr * dU);
-      stage_site<SITE>(sS, S.Drow ? S.Drow + (size_t)c1 * S.site_stride : nullptr, cD * dD * cDn);
+      contract_right<false, PPT, kT>(Y1, sX, sW2, cU, cDn, dU, dD, hl * hl * dD, hr * hr * dU);
+      stage_site<SITE, kT>(sS, S.Drow ? S.Drow + (size_t)c1 * S.site_stride : nullptr, cD * dD * cDn);
       __syncthreads();
       const int cols = hl * hl * cU, K = cDn * dD;
       mfma_gemm(cD, cols, K,
@@ -437,38 +467,36 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
     __syncthreads();
     return num;
   };
+  // the strip's moves: its plaquettes' powers, then (matter) the links whose two ends differ in
+  // occupation (the same in every thread): the horizontal links of row py (and of row L-1 in the last
+  // strip), then the vertical links of row py; the hop raises the link when the boson moves towards
+  // -x / -y
   double esum = 0.0;  // kept identical in every thread
   double eabs = 0.0;  // sum of |coefficient * ratio|: the magnitude the cancellation in esum is measured against
-  for (int px = 0; px < L - 1; ++px) {
-    for (int t = 1; t < N; ++t) {
-      const double ct = plaq[t];
-      if (ct == 0.0) continue;
-      const double term = ct * window_num(plaquette_move(px, py, t), px) / psi_strip;
-      esum += term;
-      eabs += fabs(term);
-    }
-  }
-  if (matter && hop != 0.0) {
-    // links of this strip whose two ends differ in occupation (the same in every thread): the
-    // horizontal links of row py (and of row L-1 in the last strip), then the vertical links of
-    // row py; the hop raises the link when the boson moves towards -x / -y
-    const uint8_t* occ = lk + (size_t)2 * L * L;
-    const int y_last = (py == L - 2) ? L - 1 : py;
-    for (int yy = py; yy <= y_last; ++yy)
-      for (int x = 0; x < L - 1; ++x) {
-        const int pa = occ[yy * L + x], pb = occ[yy * L + x + 1];
-        if (pa == pb) continue;
-        const double term = hop * window_num(hop_move(0, x, yy, pb ? 1 : -1), x) / psi_strip;
-        esum += term;
-        eabs += fabs(term);
-      }
-    for (int x = 0; x < L; ++x) {
-      const int pa = occ[py * L + x], pb = occ[(py + 1) * L + x];
+  const int n_plaq = (L - 1) * (N - 1), n_hor = (L - 1) * (py == L - 2 ? 2 : 1);
+  const int n_moves = n_plaq + (matter && hop != 0.0 ? n_hor + L : 0);
+  for (int w = 0; w < n_moves; ++w) {
+    Move mv;
+    int px;
+    double coef;
+    if (w < n_plaq) {
+      px = w / (N - 1);
+      const int t = 1 + w % (N - 1);
+      coef = plaq[t];
+      if (coef == 0.0) continue;
+      mv = plaquette_move(px, py, t);
+    } else {
+      const int v = w - n_plaq - n_hor, dir = v >= 0;
+      const int x = dir ? v : (w - n_plaq) % (L - 1), y = dir ? py : py + (w - n_plaq) / (L - 1);
+      const int pa = lk.at(2, x, y), pb = lk.at(2, x + !dir, y + dir);
       if (pa == pb) continue;
-      const double term = hop * window_num(hop_move(1, x, py, pb ? 1 : -1), x < L - 1 ? x : L - 2) / psi_strip;
-      esum += term;
-      eabs += fabs(term);
+      px = x < L - 1 ? x : L - 2;
+      coef = hop;
+      mv = hop_move(dir, x, y, pb ? 1 : -1);
     }
+    const double term = coef * window_num(mv, px) / psi_strip;
+    esum += term;
+    eabs += fabs(term);
   }
   if (threadIdx.x == 0) {
     part[(size_t)b * (L - 1) + py] = esum;
@@ -487,27 +515,26 @@ k_strip(Dims d, int py, const int* __restrict__ bond_all, const double* __restri
 // links_pass = 1 (matter): the strip's link moves instead, by window column (see the loop), each
 // decided against E_px and u of counter (chain, sweep, (L-1)^2 + link index, 2); E_{px+1} is formed
 // after the window's last decision.
-// BIG: fused bonds above 72, X and the staged site in the sample's global slot, as in k_strip.
-template <bool BIG>
-__global__ void __launch_bounds__(kT)
+// CH: largest boundary bond; above 36 X and the staged site in the sample's global slot, as in k_strip.
+template <int CH>
+__global__ void __launch_bounds__(StripCfg<CH>::NT)
 k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
            const int* __restrict__ bond_all, const double* __restrict__ theta,
            const int64_t* __restrict__ site_offset, uint8_t* __restrict__ links,
            const uint8_t* __restrict__ valid, const double* __restrict__ down,
            const double* __restrict__ up, double* __restrict__ scratch, int32_t* __restrict__ accepted,
            int links_pass, double* __restrict__ wbig) {
-  constexpr int ENV = BIG ? kEnvBig : kEnv;
-  constexpr int XS = BIG ? kXBig : kX;
-  constexpr int SITE = ENV / kMaxDk;
-  constexpr int PPT = (XS / 8 + kT - 1) / kT;
-  static_assert(!BIG || XS + SITE <= kBigSlot, "large-bond slot");
+  using Cfg = StripCfg<CH>;
+  constexpr bool BIG = Cfg::BIG;
+  constexpr int ENV = Cfg::ENV, XS = Cfg::XS, SITE = Cfg::SITE, PPT = Cfg::PPT, kT = Cfg::NT;
   __shared__ double lE[ENV];  // the environment stays in LDS (128 KB at the large size)
   __shared__ double lX[BIG ? 1 : XS];
   __shared__ double sW[64];
   __shared__ double sW2[64];
   __shared__ double lS[BIG ? 1 : SITE];
   __shared__ double sTb[4][16];
-  __shared__ double sRed[kW];
+  __shared__ double sRed[kT / 64];
+  __shared__ uint8_t sLk[9 * kMaxL];
   const int b = blockIdx.x;
   if (!valid[b]) return;
   double* const sE = lE;
@@ -524,7 +551,9 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
   const size_t rs = (size_t)gridDim.x * d.row_stride;
   S.Drow = S.bD ? down + (size_t)(py - 1) * rs + (size_t)b * d.row_stride : nullptr;
   S.Urow = S.bU ? up + (size_t)(L - 3 - py) * rs + (size_t)b * d.row_stride : nullptr;
-  uint8_t* lk = links + (size_t)b * d.planes * L * L;
+  uint8_t* glk = links + (size_t)b * d.planes * L * L;
+  const StripLinks lk{sLk, py};  // updated with glk
+  load_links<kT>(lk, glk, L, d.planes);
   const bool matter = d.matter != 0;
   double* gX1 = scratch + (size_t)b * ((size_t)2 * L * XS);
   double* gY1 = gX1 + (size_t)L * XS;
@@ -536,11 +565,10 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
   for (int c = L - 1; c >= 0; --c) {
     const int hl = S.hl(c), hr = S.hl(c + 1);
     const int cD = S.chiD(c), cDn = S.chiD(c + 1), cU = S.chiU(c), cUn = S.chiU(c + 1);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, c, py, plaquette_move(0, py, 0), sTb[0]);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, c, py + 1, plaquette_move(0, py, 0), sTb[1]);
-    stage_site<SITE>(sS, S.Urow ? S.Urow + (size_t)c * S.site_stride : nullptr, cU * dU * cUn);
+    gather_blocks(theta, site_offset, lk, L, N, Dk, matter, c, 1, plaquette_move(0, py, 0), sTb);
+    stage_site<SITE, kT>(sS, S.Urow ? S.Urow + (size_t)c * S.site_stride : nullptr, cU * dU * cUn);
     __syncthreads();
-    build_w(S, c, sTb[0], sTb[1], sW);
+    build_w<kT>(S, c, sTb[0], sTb[1], sW);
     {
       const int rows = cDn * hr * hr, cols = cU * dU;
       double* gy = gY1 + (size_t)c * XS;
@@ -552,8 +580,8 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
                 });
     }
     __syncthreads();
-    contract_right<true, PPT>(sX, sX, sW, cU, cDn, dU, dD, hl * hl * dD, hr * hr * dU);
-    stage_site<SITE>(sS, S.Drow ? S.Drow + (size_t)c * S.site_stride : nullptr, cD * dD * cDn);
+    contract_right<true, PPT, kT>(sX, sX, sW, cU, cDn, dU, dD, hl * hl * dD, hr * hr * dU);
+    stage_site<SITE, kT>(sS, S.Drow ? S.Drow + (size_t)c * S.site_stride : nullptr, cD * dD * cDn);
     __syncthreads();
     {
       const int cols = hl * hl * cU, K = cDn * dD;
@@ -573,7 +601,7 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
     const int c0 = px;
     const int hl = S.hl(c0), cD = S.chiD(c0), cDn = S.chiD(c0 + 1), cU = S.chiU(c0);
     double* gx = gX1 + (size_t)c0 * XS;
-    stage_site<SITE>(sS, S.Drow ? S.Drow + (size_t)c0 * S.site_stride : nullptr, cD * dD * cDn);
+    stage_site<SITE, kT>(sS, S.Drow ? S.Drow + (size_t)c0 * S.site_stride : nullptr, cD * dD * cDn);
     __syncthreads();
     const int rows = hl * hl * cU, cols = dD * cDn;
     mfma_gemm(rows, cols, cD, [&](int row, int a) { return sE[(size_t)a * rows + row]; },
@@ -585,8 +613,8 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
     const int c0 = px;
     const int hl = S.hl(c0), hr = S.hl(c0 + 1);
     const int cDn = S.chiD(c0 + 1), cU = S.chiU(c0), cUn = S.chiU(c0 + 1);
-    contract_left<false, PPT>(gX1 + (size_t)c0 * XS, sX, W, cU, cDn, dD, hl * hl * dD, hr * hr * dU);
-    stage_site<SITE>(sS, S.Urow ? S.Urow + (size_t)c0 * S.site_stride : nullptr, cU * dU * cUn);
+    contract_left<false, PPT, kT>(gX1 + (size_t)c0 * XS, sX, W, cU, cDn, dD, hl * hl * dD, hr * hr * dU);
+    stage_site<SITE, kT>(sS, S.Urow ? S.Urow + (size_t)c0 * S.site_stride : nullptr, cU * dU * cUn);
     __syncthreads();
     const int rows = cDn * hr * hr, K = cU * dU;
     mfma_gemm(rows, cUn, K,
@@ -600,9 +628,9 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
     const int c1 = px + 1;
     const int hl1 = S.hl(c1), hr1 = S.hl(c1 + 1);
     const int cD1 = S.chiD(c1), cDn1 = S.chiD(c1 + 1), cU1 = S.chiU(c1);
-    contract_right<false, PPT>(gY1 + (size_t)c1 * XS, sX, W2, cU1, cDn1, dU, dD, hl1 * hl1 * dD,
+    contract_right<false, PPT, kT>(gY1 + (size_t)c1 * XS, sX, W2, cU1, cDn1, dU, dD, hl1 * hl1 * dD,
                           hr1 * hr1 * dU);
-    stage_site<SITE>(sS, S.Drow ? S.Drow + (size_t)c1 * S.site_stride : nullptr, cD1 * dD * cDn1);
+    stage_site<SITE, kT>(sS, S.Drow ? S.Drow + (size_t)c1 * S.site_stride : nullptr, cD1 * dD * cDn1);
     __syncthreads();
     const int cols = hl1 * hl1 * cU1, K = cDn1 * dD;
     double part_num = 0.0;
@@ -614,21 +642,17 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
   };
   // W of columns px (sW) and px+1 (sW2) in the configuration mv leads to
   auto window_w = [&](int px, const Move& mv) {
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, px, py, mv, sTb[0]);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, px, py + 1, mv, sTb[1]);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, px + 1, py, mv, sTb[2]);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, px + 1, py + 1, mv, sTb[3]);
+    gather_blocks(theta, site_offset, lk, L, N, Dk, matter, px, 2, mv, sTb);
     __syncthreads();
-    build_w(S, px, sTb[0], sTb[1], sW);
-    build_w(S, px + 1, sTb[2], sTb[3], sW2);
+    build_w<kT>(S, px, sTb[0], sTb[1], sW);
+    build_w<kT>(S, px + 1, sTb[2], sTb[3], sW2);
     __syncthreads();
   };
   // E_{px+1} of the current configuration: (X1_px W_px) U_px
   auto advance = [&](int px) {
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, px, py, plaquette_move(0, py, 0), sTb[0]);
-    gather_block(theta, site_offset, lk, L, N, Dk, matter, px, py + 1, plaquette_move(0, py, 0), sTb[1]);
+    gather_blocks(theta, site_offset, lk, L, N, Dk, matter, px, 1, plaquette_move(0, py, 0), sTb);
     __syncthreads();
-    build_w(S, px, sTb[0], sTb[1], sW);
+    build_w<kT>(S, px, sTb[0], sTb[1], sW);
     __syncthreads();
     left_half(px, sW);
   };
@@ -650,14 +674,15 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
       if (psi != 0.0 && u < ratio * ratio) {
         // s <- P_p^t s; sE already holds E_{px+1} of the new configuration
         if (threadIdx.x == 0) {
-          uint8_t* h0 = lk + (size_t)py * L + px;             // h(px, py)
-          uint8_t* h1 = lk + (size_t)(py + 1) * L + px;       // h(px, py+1)
-          uint8_t* v0 = lk + (size_t)L * L + py * L + px;     // v(px, py)
-          uint8_t* v1 = v0 + 1;                               // v(px+1, py)
-          *h0 = (uint8_t)((*h0 + t) % N);
-          *v1 = (uint8_t)((*v1 + t) % N);
-          *h1 = (uint8_t)((*h1 + N - t) % N);
-          *v0 = (uint8_t)((*v0 + N - t) % N);
+          auto shift = [&](int plane, int x, int y, int by) {
+            const uint8_t n = (uint8_t)((lk.at(plane, x, y) + by) % N);
+            lk.at(plane, x, y) = n;
+            glk[(size_t)plane * L * L + y * L + x] = n;
+          };
+          shift(0, px, py, t);
+          shift(1, px + 1, py, t);
+          shift(0, px, py + 1, N - t);
+          shift(1, px, py, N - t);
         }
         psi = num;
         ++nacc;
@@ -675,9 +700,8 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
         else if (m == 1) { dir = 0; x = px; y = py; }
         else if (m == 2) { if (py != L - 2) continue; dir = 0; x = px; y = L - 1; }
         else { if (px != L - 2) continue; dir = 1; x = L - 1; y = py; }
-        uint8_t* occ = lk + (size_t)2 * L * L;
-        const int ia = y * L + x, ib = (y + (dir == 1)) * L + x + (dir == 0);
-        const int pa = occ[ia], pb = occ[ib];
+        const int xb = x + (dir == 0), yb = y + (dir == 1);
+        const int pa = lk.at(2, x, y), pb = lk.at(2, xb, yb);
         if (pa == pb) continue;  // same in every thread
         const int link = dir == 0 ? y * (L - 1) + x : L * (L - 1) + y * L + x;
         const uint64_t cnt = (uint64_t)((L - 1) * (L - 1) + link);
@@ -689,10 +713,13 @@ k_strip_mc(Dims d, int py, int sweep, uint64_t seed, uint64_t stream,
         const double ratio = num / psi;
         if (psi != 0.0 && u < ratio * ratio) {
           if (threadIdx.x == 0) {
-            uint8_t* l = lk + (size_t)dir * L * L + y * L + x;
-            *l = (uint8_t)((*l + (step > 0 ? 1 : N - 1)) % N);
-            occ[ia] = (uint8_t)pb;
-            occ[ib] = (uint8_t)pa;
+            auto put = [&](int plane, int xx, int yy, int n) {
+              lk.at(plane, xx, yy) = (uint8_t)n;
+              glk[(size_t)plane * L * L + yy * L + xx] = (uint8_t)n;
+            };
+            put(dir, x, y, (lk.at(dir, x, y) + (step > 0 ? 1 : N - 1)) % N);
+            put(2, x, y, pb);
+            put(2, xb, yb, pa);
           }
           psi = num;
           ++nacc;
@@ -769,21 +796,52 @@ hipError_t launch_mirror_proj(const Dims& d, const double* proj, const uint8_t* 
   return hipGetLastError();
 }
 
-hipError_t launch_strip(const Dims& d, int py, const DeviceTables& t, const double* proj,
-                        const double* theta, const uint8_t* links, const uint8_t* valid, int B,
-                        const double* down, const double* up, const double* plaq, double hop,
-                        double* scratch, double* part, double* pabs, hipStream_t s, double* wbig) {
+// kernel launcher F<CH> of the class that holds the handle's boundary bonds
+#define GIPEPS_STRIP_CLASS(F, ...)                     \
+  switch (row_class(d.maxN, d.Dk)) {                   \
+    case 16: return F<8>(__VA_ARGS__);                 \
+    case 32: return F<16>(__VA_ARGS__);                \
+    case 48: return F<24>(__VA_ARGS__);                \
+    case kMaxN: return F<kMaxN / 2>(__VA_ARGS__);      \
+    case kMaxNBig: return F<kMaxNBig / 2>(__VA_ARGS__); \
+    default: return hipErrorInvalidValue;              \
+  }
+
+int strips_per_launch(const Dims& d) {
+  const int cls = row_class(d.maxN, d.Dk);
+  const int xs = cls == 16 ? StripCfg<8>::XS : cls == 32 ? StripCfg<16>::XS : cls == 48 ? StripCfg<24>::XS : 0;
+  return xs ? kX / xs : 1;
+}
+
+template <int CH>
+static hipError_t launch_strip_t(const Dims& d, int py, int strips, const DeviceTables& t, const double* proj,
+                                 const double* theta, const uint8_t* links, const uint8_t* valid, int B,
+                                 const double* down, const double* up, const double* plaq, double hop, double* scratch,
+                                 double* part, double* pabs, hipStream_t s, double* wbig) {
+  hipLaunchKernelGGL(k_strip<CH>, dim3(B, strips), dim3(StripCfg<CH>::NT), 0, s, d, py, t.bond, proj, theta,
+                     t.site_offset, links, valid, down, up, plaq, hop, scratch, part, pabs, wbig);
+  return hipGetLastError();
+}
+
+hipError_t launch_strip(const Dims& d, int py, int strips, const DeviceTables& t, const double* proj,
+                        const double* theta, const uint8_t* links, const uint8_t* valid, int B, const double* down,
+                        const double* up, const double* plaq, double hop, double* scratch, double* part, double* pabs,
+                        hipStream_t s, double* wbig) {
   if (B == 0) return hipSuccess;
   // The strip contractions stay FP64 in the mixed path too: with FP32 arithmetic the strip
   // amplitudes of random-sign tensors cancel enough to move E/site by ~4e-2 relative.
-  if (d.maxN > kMaxN) {
-    if (d.Dk != 2 || d.maxN > kMaxNBig || !wbig) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_strip<true>, dim3(B), dim3(kT), 0, s, d, py, t.bond, proj, theta,
-                       t.site_offset, links, valid, down, up, plaq, hop, scratch, part, pabs, wbig);
-  } else {
-    hipLaunchKernelGGL(k_strip<false>, dim3(B), dim3(kT), 0, s, d, py, t.bond, proj, theta,
-                       t.site_offset, links, valid, down, up, plaq, hop, scratch, part, pabs, wbig);
-  }
+  if ((d.maxN > kMaxN && !wbig) || strips > strips_per_launch(d)) return hipErrorInvalidValue;
+  GIPEPS_STRIP_CLASS(launch_strip_t, d, py, strips, t, proj, theta, links, valid, B, down, up, plaq, hop, scratch, part,
+                     pabs, s, wbig)
+}
+
+template <int CH>
+static hipError_t launch_strip_mc_t(const Dims& d, int py, int sweep, uint64_t seed, uint64_t stream,
+                                    const DeviceTables& t, const double* theta, uint8_t* links, const uint8_t* valid,
+                                    int B, const double* down, const double* up, double* scratch, int32_t* accepted,
+                                    int links_pass, hipStream_t s, double* wbig) {
+  hipLaunchKernelGGL(k_strip_mc<CH>, dim3(B), dim3(StripCfg<CH>::NT), 0, s, d, py, sweep, seed, stream, t.bond, theta,
+                     t.site_offset, links, valid, down, up, scratch, accepted, links_pass, wbig);
   return hipGetLastError();
 }
 
@@ -793,16 +851,11 @@ hipError_t launch_strip_mc(const Dims& d, int py, int sweep, uint64_t seed, uint
                            double* scratch, int32_t* accepted, int links_pass, hipStream_t s,
                            double* wbig) {
   if (B == 0 || d.N < 2) return hipSuccess;
-  if (d.maxN > kMaxN) {
-    if (d.Dk != 2 || d.maxN > kMaxNBig || !wbig) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_strip_mc<true>, dim3(B), dim3(kT), 0, s, d, py, sweep, seed, stream, t.bond, theta,
-                       t.site_offset, links, valid, down, up, scratch, accepted, links_pass, wbig);
-  } else {
-    hipLaunchKernelGGL(k_strip_mc<false>, dim3(B), dim3(kT), 0, s, d, py, sweep, seed, stream, t.bond, theta,
-                       t.site_offset, links, valid, down, up, scratch, accepted, links_pass, wbig);
-  }
-  return hipGetLastError();
+  if (d.maxN > kMaxN && !wbig) return hipErrorInvalidValue;
+  GIPEPS_STRIP_CLASS(launch_strip_mc_t, d, py, sweep, seed, stream, t, theta, links, valid, B, down, up, scratch,
+                     accepted, links_pass, s, wbig)
 }
+#undef GIPEPS_STRIP_CLASS
 
 hipError_t launch_eloc_final(const Dims& d, const uint8_t* links, const uint8_t* valid, int B,
                              const double* elec, double mass, const double* part, const double* pabs,

@@ -125,7 +125,7 @@ size_t qslot_doubles(const Dims& d) {
 }
 
 
-CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what) {
+CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what, bool split) {
   const Dims& d = h->d;
   const size_t Bz = (size_t)B, L = d.L, n = (size_t)h->n_params, P4 = d.P4, ns = d.n_sites;
   size_t S = 1;
@@ -140,9 +140,13 @@ CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what) {
   };
   w.states = take(cxs * Bz * 2 * (L + 1) * S);
   w.expo = take(sizeof(double) * Bz * 2 * (L + 1));
-  w.gscr = take(cxs * Bz * L * W);
-  w.wscr = take(cx_work_global(d) ? cxs * Bz * 2 * W : 0);
-  w.base_end = off;
+  w.slots = split ? cx_split_slots(d, B) : B;
+  w.gscr = take(cxs * w.slots * L * W);
+  w.wscr = take(cx_work_global(d) ? cxs * w.slots * 2 * W : 0);
+  w.epart = take(w.slots > B ? cxb * Bz * (L - 1) : 0);
+  // the slots beyond the batch take the same bytes for either precision of the states
+  off += (size_t)(w.slots - B) * (cxb - cxs) * (cx_work_global(d) ? L + 2 : L) * W;
+  w.base_end = off = align256(off);
   if (what & PEPS_WS_SAMPLE) {
     w.lprop = take((size_t)d.planes * L * L * Bz);
     w.laprop = take(sizeof(double) * Bz);
@@ -173,6 +177,12 @@ CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what) {
   }
   w.total = off;
   return w;
+}
+
+// The split layout when `have` bytes hold it up to base_end (base) or whole, else one slot per sample.
+CxWs cx_ws_fit(const peps_handle* h, int B, uint32_t what, size_t have, bool base) {
+  const CxWs w = cx_ws_layout(h, B, what, true);
+  return have >= (base ? w.base_end : w.total) ? w : cx_ws_layout(h, B, what, false);
 }
 
 WsLayout ws_layout(const peps_handle* h, int B, uint32_t what) {
@@ -376,7 +386,9 @@ int peps_workspace_bytes(const peps_handle* h, int32_t B, uint32_t what, size_t*
   if (what & ~uint32_t(PEPS_WS_AMPLITUDE | PEPS_WS_ENERGY | PEPS_WS_LOGDERIV | PEPS_WS_SAMPLE | PEPS_WS_TVMC))
     return PEPS_ERR_ARG;
   if (is_cx(h->dtype)) {
-    *bytes = (B == 0 || what == 0) ? 0 : cx_ws_layout(h, B, what).total;
+    *bytes = B == 0 || what == 0 ? 0
+             : std::max(cx_ws_layout(h, B, what, false).total,
+                        cx_ws_layout(h, B, what & ~uint32_t(PEPS_WS_SAMPLE), true).total);
     return PEPS_OK;
   }
   if (what & PEPS_WS_TVMC) return PEPS_ERR_ARG;  // the tVMC buffers belong to complex handles
@@ -580,7 +592,7 @@ int peps_metropolis(peps_handle* h, const double* theta, uint64_t seed, uint64_t
   const bool cplx = is_cx(h->dtype);
   size_t need = 0, o_lprop = 0, o_laprop = 0, o_sgprop = 0, o_moved = 0;
   if (cplx) {
-    const CxWs w = cx_ws_layout(h, B, PEPS_WS_AMPLITUDE | PEPS_WS_SAMPLE);
+    const CxWs w = cx_ws_layout(h, B, PEPS_WS_AMPLITUDE | PEPS_WS_SAMPLE, false);
     need = w.total;
     o_lprop = w.lprop;
     o_laprop = w.laprop;
@@ -661,7 +673,7 @@ int peps_metropolis_strip(peps_handle* h, const double* theta, uint64_t seed, ui
     // finally ln|Psi| (and the row states) of the final chains
     if (h->d.N < 2) return PEPS_ERR_UNSUPPORTED;
     if (B == 0) return PEPS_OK;
-    const CxWs w = cx_ws_layout(h, B, PEPS_WS_AMPLITUDE | PEPS_WS_SAMPLE);
+    const CxWs w = cx_ws_layout(h, B, PEPS_WS_AMPLITUDE | PEPS_WS_SAMPLE, false);
     if (!ws_ok(ws, ws_bytes, w.total)) return PEPS_ERR_WORKSPACE;
     if (int st = ensure_device(h)) return st;
     hipStream_t s = (hipStream_t)stream;
@@ -1033,7 +1045,7 @@ int peps_cx_amplitude(peps_handle* h, const double* proj, const uint8_t* valid, 
   if (!h || B < 0 || (B > 0 && (!proj || !valid || !log_abs || !phase))) return PEPS_ERR_ARG;
   if (!is_cx(h->dtype)) return PEPS_ERR_ARG;
   if (B == 0) return PEPS_OK;
-  const CxWs w = cx_ws_layout(h, B, PEPS_WS_AMPLITUDE);
+  const CxWs w = cx_ws_layout(h, B, PEPS_WS_AMPLITUDE, false);
   if (!ws_ok(ws, ws_bytes, w.base_end)) return PEPS_ERR_WORKSPACE;
   if (int st = ensure_device(h)) return st;
   hipStream_t s = (hipStream_t)stream;
@@ -1053,14 +1065,15 @@ int peps_cx_local_energy(peps_handle* h, const double* theta, const uint8_t* lin
   if (!h || B < 0 || (B > 0 && (!theta || !links || !proj || !valid || !e_loc))) return PEPS_ERR_ARG;
   if (!is_cx(h->dtype)) return PEPS_ERR_ARG;
   if (B == 0) return PEPS_OK;
-  const CxWs w = cx_ws_layout(h, B, PEPS_WS_AMPLITUDE);
+  const CxWs w = cx_ws_fit(h, B, PEPS_WS_AMPLITUDE, ws_bytes, true);
   if (!ws_ok(ws, ws_bytes, w.base_end)) return PEPS_ERR_WORKSPACE;
   if (h->last_amp_ws != ws || h->last_amp_B != B) return PEPS_ERR_STATE;
   if (int st = ensure_device(h)) return st;
   hipStream_t s = (hipStream_t)stream;
   return hip_status(timed(h, PEPS_K_STRIP, s, [&] {
     return launch_cx_eloc(h->d, h->t, theta, links, proj, valid, B, (const double*)((char*)ws + w.states), e_loc,
-                          (double*)((char*)ws + w.gscr), (double*)((char*)ws + w.wscr), s);
+                          (double*)((char*)ws + w.gscr), (double*)((char*)ws + w.wscr), w.slots,
+                          (double*)((char*)ws + w.epart), s);
   }));
 }
 
@@ -1069,7 +1082,7 @@ int peps_cx_logderiv(peps_handle* h, const double* proj, const uint8_t* valid, i
   if (!h || B < 0 || (B > 0 && (!proj || !valid || !O))) return PEPS_ERR_ARG;
   if (!is_cx(h->dtype)) return PEPS_ERR_ARG;
   if (B == 0) return PEPS_OK;
-  const CxWs w = cx_ws_layout(h, B, PEPS_WS_AMPLITUDE);
+  const CxWs w = cx_ws_fit(h, B, PEPS_WS_AMPLITUDE, ws_bytes, true);
   if (!ws_ok(ws, ws_bytes, w.base_end)) return PEPS_ERR_WORKSPACE;
   if (h->last_amp_ws != ws || h->last_amp_B != B) return PEPS_ERR_STATE;
   if (int st = ensure_device(h)) return st;
@@ -1077,7 +1090,7 @@ int peps_cx_logderiv(peps_handle* h, const double* proj, const uint8_t* valid, i
   char* base = (char*)ws;
   return hip_status(timed(h, PEPS_K_ADJOINT, s, [&] {
     return launch_cx_logderiv(h->d, proj, valid, B, (const double*)(base + w.states), (double*)(base + w.gscr), O,
-                              (double*)(base + w.wscr), s);
+                              (double*)(base + w.wscr), w.slots, s);
   }));
 }
 
@@ -1167,7 +1180,7 @@ int tvmc_rhs(peps_handle* h, const double* O, const int32_t* block_id, const uin
   if (B > 0 && (!O || !block_id || !valid || !e_loc || !log_abs || !xdot)) return PEPS_ERR_ARG;
   if (!is_cx(h->dtype)) return PEPS_ERR_ARG;
   if (B == 0) return PEPS_OK;
-  const CxWs w = cx_ws_layout(h, B, PEPS_WS_TVMC);
+  const CxWs w = cx_ws_fit(h, B, PEPS_WS_TVMC, ws_bytes, false);
   if (!ws_ok(ws, ws_bytes, w.total)) return PEPS_ERR_WORKSPACE;
   if (int st = ensure_device(h)) return st;
   int it = 0;
@@ -1187,7 +1200,7 @@ int tvmc_step(peps_handle* h, double* theta, const uint8_t* links, int32_t B, in
   if (B > 0 && (!theta || !links)) return PEPS_ERR_ARG;
   if (!is_cx(h->dtype)) return PEPS_ERR_ARG;
   if (B == 0) return PEPS_OK;
-  const CxWs w = cx_ws_layout(h, B, PEPS_WS_TVMC);
+  const CxWs w = cx_ws_fit(h, B, PEPS_WS_TVMC, ws_bytes, false);
   if (!ws_ok(ws, ws_bytes, w.total)) return PEPS_ERR_WORKSPACE;
   if (int st = ensure_device(h)) return st;
   hipStream_t s = (hipStream_t)stream;
@@ -1202,12 +1215,13 @@ int tvmc_step(peps_handle* h, double* theta, const uint8_t* links, int32_t B, in
   double* xdot = (double*)(base + w.xdot);
   double* theta1 = (double*)(base + w.theta1);
   const int64_t n = h->n_params;
-  // alphadot at parameters th: projection, amplitude, O, E_loc, then the linear system
+  // alphadot at parameters th: projection, amplitude, O, E_loc, then the linear system (the calls see the
+  // workspace up to base_end: their layout is then this one's)
   auto velocity = [&](const double* th, double* en, int* it) {
     int st = peps_cx_project(h, th, links, B, proj, bid, valid, s);
-    if (st == PEPS_OK) st = peps_cx_amplitude(h, proj, valid, B, la, phase, ws, ws_bytes, s);
-    if (st == PEPS_OK) st = peps_cx_logderiv(h, proj, valid, B, O, ws, ws_bytes, s);
-    if (st == PEPS_OK) st = peps_cx_local_energy(h, th, links, proj, valid, B, eloc, ws, ws_bytes, s);
+    if (st == PEPS_OK) st = peps_cx_amplitude(h, proj, valid, B, la, phase, ws, w.base_end, s);
+    if (st == PEPS_OK) st = peps_cx_logderiv(h, proj, valid, B, O, ws, w.base_end, s);
+    if (st == PEPS_OK) st = peps_cx_local_energy(h, th, links, proj, valid, B, eloc, ws, w.base_end, s);
     if (st == PEPS_OK)
       st = cx_rhs(h, w, base, O, bid, valid, eloc, la, B, weights, shift, max_iter, rtol, xdot, en, it, nullptr, s);
     return st;

@@ -272,10 +272,12 @@ hipError_t launch_close(const Dims& d, const int* bond_last, const double* proj,
                         double* log_abs, double* sign, hipStream_t s);
 
 // Complex exact-contraction path (k_complex.hip); complex vectors are interleaved (re, im) doubles.
-size_t cx_lds_bytes(const Dims& d, int which);  // 0: states / logderiv kernels, 1: local energy
+size_t cx_lds_bytes(const Dims& d, int which);  // 0: states / logderiv kernels, 1: local energy, 2: strip sampler
 size_t cx_work(const Dims& d);         // Dk^(L+1): entries of one working state
 // bytes of one complex entry of the contractions' states: 8 (complex64) or 16 (complex128)
 inline size_t cx_elem_bytes(const Dims& d) { return d.cx32 ? 2 * sizeof(float) : 2 * sizeof(double); }
+// slots of backward and working states that E_loc and the log-derivatives of B samples run in (>= B)
+int cx_split_slots(const Dims& d, int B);
 bool cx_work_global(const Dims& d);    // working states above kCxMaxWork live in a global slot (wscr)
 hipError_t launch_cx_project(const Dims& d, const DeviceTables& t, const double* theta, const uint8_t* links,
                              int B, double* proj, int32_t* block_id, uint8_t* valid, hipStream_t s);
@@ -283,13 +285,13 @@ hipError_t launch_cx_states(const Dims& d, const double* proj, const uint8_t* va
                             double* expo, double* log_abs, double* phase, double* wscr, hipStream_t s);
 hipError_t launch_cx_eloc(const Dims& d, const DeviceTables& t, const double* theta, const uint8_t* links,
                           const double* proj, const uint8_t* valid, int B, const double* states, double* e_loc,
-                          double* gscr, double* wscr, hipStream_t s);
+                          double* gscr, double* wscr, int slots, double* epart, hipStream_t s);
 // one strip-ratio Metropolis sweep of complex chains (links updated in place, accepted added to)
 hipError_t launch_cx_strip_mc(const Dims& d, const DeviceTables& t, const double* theta, uint8_t* links,
                               const uint8_t* valid, int B, double* states, double* gscr, double* wscr,
                               uint64_t seed, uint64_t stream, int sweep, int32_t* accepted, hipStream_t s);
 hipError_t launch_cx_logderiv(const Dims& d, const double* proj, const uint8_t* valid, int B, const double* states,
-                              double* gscr, double* O, double* wscr, hipStream_t s);
+                              double* gscr, double* O, double* wscr, int slots, hipStream_t s);
 hipError_t launch_cx_weights(int B, int mode, const double* log_abs, const uint8_t* valid, double* w,
                              hipStream_t s);
 int cx_blocks_per_site(const Dims& d);
@@ -312,8 +314,10 @@ hipError_t launch_cx_axpy(int64_t n, double ar, double ai, const double* z, cons
 struct CxWs {
   size_t states;   // double [B][2(L+1)][Dk^L][2]   V_0..V_L, Top_0..Top_L
   size_t expo;     // double [B][2(L+1)]            their power-of-two exponents
-  size_t gscr;     // double [B][L][Dk^(L+1)][2]    backward states of one row
-  size_t wscr;     // double [B][2][Dk^(L+1)][2]    working states (only above kCxMaxWork entries)
+  int slots;       // slots of gscr and wscr: B, or cx_split_slots when the workspace holds them
+  size_t gscr;     // double [slots][L][Dk^(L+1)][2]  backward states of one row
+  size_t wscr;     // double [slots][2][Dk^(L+1)][2]  working states (only above kCxMaxWork entries)
+  size_t epart;    // double [B][L-1][2]            E_loc per pair of rows (only if slots > B)
   size_t w;        // double [B]                     sample weights
   size_t ov;       // double [B][2]                  O_b . v
   size_t sc;       // double [64]                    <E>, <w O.v>, CG scalars
@@ -337,6 +341,6 @@ struct CxWs {
   size_t moved;    // uint8 [B]
   size_t base_end, total;
 };
-CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what);
+CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what, bool split);
 
 }  // namespace gipeps

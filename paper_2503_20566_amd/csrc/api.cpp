@@ -156,7 +156,7 @@ CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what, bool split) {
   if (what & PEPS_WS_TVMC) {
     w.w = take(sizeof(double) * Bz);
     w.ov = take(cxb * Bz);
-    w.sc = take(sizeof(double) * 64);
+    w.sc = take(sizeof(double) * kCxScalars);
     w.ioff = take(sizeof(int32_t) * ns * (size_t)(d.N * d.N * d.N + 1));
     w.ilist = take(sizeof(int32_t) * ns * Bz);
     w.omean = take(cxb * n);
@@ -1123,43 +1123,29 @@ int cx_rhs(peps_handle* h, const gipeps::CxWs& w, char* base, const double* O, c
     e = timed(h, PEPS_K_SR, s, [&] {
       return launch_cx_force(h->d, h->t, n, B, ioff, ilist, wt, O, e_loc, sc, omean, g, s);
     });
-  double em[2] = {0.0, 0.0};
-  if (e == hipSuccess) e = host(sc, em, 2);
-  if (energy) {
-    energy[0] = em[0];
-    energy[1] = em[1];
-  }
-  // conjugate gradients for (S + shift I) y = g from y = 0 (Hermitian inner products)
-  if (e == hipSuccess) e = launch_fill(y, 2 * (size_t)n, 0.0, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(r, g, sizeof(double) * 2 * n, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(p, g, sizeof(double) * 2 * n, hipMemcpyDeviceToDevice, s);
-  double two[2] = {0.0, 0.0};
-  if (e == hipSuccess) e = launch_cx_dot(n, r, r, sc + 4, s);
-  if (e == hipSuccess) e = host(sc + 4, two, 2);
-  const double f2 = two[0];
-  double rr = f2;
+  // conjugate gradients for (S + shift I) y = g from y = 0 (Hermitian inner products).  The kernels of an
+  // iteration past the end do nothing, so the host looks at the scalars once in kCheck iterations: with two
+  // readbacks in each, the device was idle for 50 of an iteration's 108 us.
+  constexpr int kCheck = 8;
+  if (e == hipSuccess) e = launch_cx_cg_start(n, g, y, r, sc, s);
+  double state[kCxScalars] = {};
+  double rr = 0.0, f2 = 0.0;
   int k = 0;
-  while (e == hipSuccess && f2 > 0.0 && k < max_iter && rr > rtol * rtol * f2) {
-    e = timed(h, PEPS_K_SR, s, [&] {
-      return launch_cx_matvec(h->d, h->t, n, B, bid, ioff, ilist, wt, O, omean, shift, p, ov, sc, q, s);
-    });
-    if (e == hipSuccess) e = launch_cx_dot(n, p, q, sc + 6, s);
-    if (e == hipSuccess) e = host(sc + 6, two, 2);
-    if (e != hipSuccess || !(two[0] > 0.0)) break;  // breakdown: y and r left unchanged
-    const double alpha = rr / two[0];
-    e = launch_cx_axpy(n, alpha, 0.0, p, y, y, s);
-    if (e == hipSuccess) e = launch_cx_axpy(n, -alpha, 0.0, q, r, r, s);
-    if (e == hipSuccess) e = launch_cx_dot(n, r, r, sc + 8, s);
-    if (e == hipSuccess) e = host(sc + 8, two, 2);
+  bool done = false;
+  for (int next = 0; e == hipSuccess;) {
+    for (const int last = std::min(max_iter, next + kCheck); next < last && e == hipSuccess; ++next)
+      e = timed(h, PEPS_K_SR, s, [&] {
+        return launch_cx_cg_iteration(h->d, h->t, n, B, bid, ioff, ilist, wt, O, omean, shift, next, rtol * rtol, y, r,
+                                      p, q, ov, sc, s);
+      });
+    if (e == hipSuccess) e = host(sc, state, kCxScalars);
     if (e != hipSuccess) break;
-    const double rr_new = two[0];
-    ++k;
-    if (rr_new <= rtol * rtol * f2) {
-      rr = rr_new;
-      break;
-    }
-    e = launch_cx_axpy(n, rr_new / rr, 0.0, p, r, p, s);  // p = r + beta p
-    rr = rr_new;
+    cx_cg_state(state, k, rr, f2, done);
+    if (done || next >= max_iter || !(f2 > 0.0) || !(rr > rtol * rtol * f2)) break;
+  }
+  if (energy) {
+    energy[0] = state[0];
+    energy[1] = state[1];
   }
   // alphadot = -i y
   if (e == hipSuccess) e = launch_fill(xdot, 2 * (size_t)n, 0.0, s);

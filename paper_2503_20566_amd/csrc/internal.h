@@ -301,11 +301,15 @@ hipError_t launch_cx_index(const Dims& d, int B, const int32_t* bid, const doubl
 hipError_t launch_cx_force(const Dims& d, const DeviceTables& t, int64_t n, int B, const int32_t* off,
                            const int32_t* list, const double* w, const double* O, const double* e_loc, double* sc,
                            double* omean, double* g, hipStream_t s);
-hipError_t launch_cx_matvec(const Dims& d, const DeviceTables& t, int64_t n, int B, const int32_t* bid,
-                            const int32_t* off, const int32_t* list, const double* w, const double* O,
-                            const double* omean, double shift, const double* v, double* ov, double* sc, double* out,
-                            hipStream_t s);
-hipError_t launch_cx_dot(int64_t n, const double* a, const double* b, double* out, hipStream_t s);
+// Conjugate gradients of the tVMC system: y = 0, r = g; iteration k, which does nothing once r.r is within
+// rtol2 of its start or p.q was not positive; and what the scalars sc (kCxScalars doubles) then say
+constexpr int kCxScalars = 64;
+hipError_t launch_cx_cg_start(int64_t n, const double* g, double* y, double* r, double* sc, hipStream_t s);
+hipError_t launch_cx_cg_iteration(const Dims& d, const DeviceTables& t, int64_t n, int B, const int32_t* bid,
+                                  const int32_t* off, const int32_t* list, const double* w, const double* O,
+                                  const double* omean, double shift, int k, double rtol2, double* y, double* r,
+                                  double* p, double* q, double* ov, double* sc, hipStream_t s);
+void cx_cg_state(const double* sc, int& iterations, double& rr, double& f2, bool& done);
 hipError_t launch_cx_axpy(int64_t n, double ar, double ai, const double* z, const double* x, double* y,
                           hipStream_t s);
 
@@ -320,7 +324,7 @@ struct CxWs {
   size_t epart;    // double [B][L-1][2]            E_loc per pair of rows (only if slots > B)
   size_t w;        // double [B]                     sample weights
   size_t ov;       // double [B][2]                  O_b . v
-  size_t sc;       // double [64]                    <E>, <w O.v>, CG scalars
+  size_t sc;       // double [kCxScalars]            <E>, CG scalars
   size_t ioff;     // int32 [L*L][N^3+1]             per site: first index of each block's samples
   size_t ilist;    // int32 [L*L][B]                 per site: the weighted samples, by block
   size_t omean;    // double [n][2]

@@ -60,6 +60,15 @@ __device__ inline double block_sum(double v, double* red) {
   return s;
 }
 
+// Quotients by a number that is known at run time only, by a product: exact for e d < 2^32 (e < 2^14 and
+// d < 2^14 here).  The division itself is some forty instructions, more than an element's own work.
+struct FastDiv {
+  unsigned d, m;
+  __device__ explicit FastDiv(int div) : d((unsigned)div), m(0xFFFFFFFFu / (unsigned)div + 1u) {}
+  __device__ __forceinline__ int quot(int e) const { return d == 1u ? e : (int)__umulhi((unsigned)e, m); }
+  __device__ __forceinline__ int rem(int e, int q) const { return e - q * (int)d; }
+};
+
 // Register-tiled product over a workgroup: out(i, j) = sum_{k<K} a(i, k) b(k, j) for i < M, j < N.
 // Each thread owns TM x TN output tiles (round-robin over the threads, consecutive threads along j),
 // so an operand element fetched once feeds TM or TN multiply-adds.  The k sum runs in ascending
@@ -141,6 +150,39 @@ __device__ __forceinline__ void tile_gemm_sync(int M, int N, int K, FA a, FB b, 
 
 typedef double dvec4 __attribute__((ext_vector_type(4)));
 
+// The k loop of NT tiles (16 x 16 outputs each, c[q]) of a product on the matrix cores: lane l supplies a(q, k)
+// and b(q, k), its row's and its column's entries at k = 4 step + l / 16, for every k < K.  Two steps' operands
+// are loaded before their products, so that a step does not wait for its own LDS reads (they were most of a
+// tile's time: a step's product takes 32 cycles, its reads over a hundred).  Ascending k for every output.
+template <int NT, class FA, class FB>
+__device__ __forceinline__ void mfma_k_loop(dvec4 (&c)[NT], int K, int lk, FA a, FB b) {
+  constexpr int U = 2;
+  int k0 = 0;
+  for (; k0 + 4 * U <= K; k0 += 4 * U) {
+    double av[U][NT], bv[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < NT; ++q) {
+        av[u][q] = a(q, k0 + 4 * u + lk);
+        bv[u][q] = b(q, k0 + 4 * u + lk);
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < NT; ++q) c[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][q], bv[u][q], c[q], 0, 0, 0);
+  }
+  for (; k0 < K; k0 += 4) {
+    const int k = min(k0 + lk, K - 1);
+    const bool kin = k0 + lk < K;
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+      const double av = a(q, k), bv = b(q, k);
+      c[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(kin ? av : 0.0, kin ? bv : 0.0, c[q], 0, 0, 0);
+    }
+  }
+}
+
 // FP64 product on the matrix cores (v_mfma_f64_16x16x4f64): out(i, j) = sum_k a(i, k) b(k, j).
 // Each wave takes 16 x 16 output tiles, two at a time (two independent accumulation chains).  Per
 // 4-deep k step lane l supplies A[i0 + l%16][k0 + l/16] and B[k0 + l/16][j0 + l%16] and afterwards
@@ -158,18 +200,18 @@ __device__ __forceinline__ void mfma_gemm(int M, int N, int K, FA a, FB b, FS si
     const bool two = t2 < tiles;  // wave-uniform
     const int i0 = (t / tn) * 16, j0 = (t % tn) * 16;
     const int i1 = two ? (t2 / tn) * 16 : i0, j1 = two ? (t2 % tn) * 16 : j0;
-    dvec4 c0 = {0.0, 0.0, 0.0, 0.0}, c1 = {0.0, 0.0, 0.0, 0.0};
-    for (int k0 = 0; k0 < K; k0 += 4) {
-      const int k = k0 + lk;
-      const bool kin = k < K;
-      const double a0 = (kin && i0 + li < M) ? a(i0 + li, k) : 0.0;
-      const double b0 = (kin && j0 + li < N) ? b(k, j0 + li) : 0.0;
-      c0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, c0, 0, 0, 0);
-      if (two) {
-        const double a1 = (kin && i1 + li < M) ? a(i1 + li, k) : 0.0;
-        const double b1 = (kin && j1 + li < N) ? b(k, j1 + li) : 0.0;
-        c1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, c1, 0, 0, 0);
-      }
+    // rows and columns beyond the product: the last one's entries, whose outputs are not used
+    const int ia[2] = {min(i0 + li, M - 1), min(i1 + li, M - 1)}, jb[2] = {min(j0 + li, N - 1), min(j1 + li, N - 1)};
+    dvec4 c0, c1;
+    if (two) {
+      dvec4 c[2] = {};
+      mfma_k_loop<2>(c, K, lk, [&](int q, int k) { return a(ia[q], k); }, [&](int q, int k) { return b(k, jb[q]); });
+      c0 = c[0];
+      c1 = c[1];
+    } else {
+      dvec4 c[1] = {};
+      mfma_k_loop<1>(c, K, lk, [&](int, int k) { return a(ia[0], k); }, [&](int, int k) { return b(k, jb[0]); });
+      c0 = c[0];
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -201,12 +243,10 @@ __device__ __forceinline__ void mfma_gemm_sync(int M, int N, int K, FA a, FB b, 
     const int t = wave + q * nw;
     if (t < tiles) {
       const int i0 = (t / tn) * 16, j0 = (t % tn) * 16;
-      for (int k0 = 0; k0 < K; k0 += 4) {
-        const int k = k0 + lk;
-        const double av = (k < K && i0 + li < M) ? a(i0 + li, k) : 0.0;
-        const double bv = (k < K && j0 + li < N) ? b(k, j0 + li) : 0.0;
-        c[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, c[q], 0, 0, 0);
-      }
+      const int ia = min(i0 + li, M - 1), jb = min(j0 + li, N - 1);
+      dvec4 ct[1] = {c[q]};
+      mfma_k_loop<1>(ct, K, lk, [&](int, int k) { return a(ia, k); }, [&](int, int k) { return b(k, jb); });
+      c[q] = ct[0];
     }
   }
   __syncthreads();
@@ -234,6 +274,7 @@ __device__ __forceinline__ void mfma_gemm_staged(int M, int N, int K, FG gload, 
   const int tn = (N + 15) / 16, tiles = ((M + 15) / 16) * tn;
   const int li = lane & 15, lk = lane >> 4;
   const int nch = (K + KC - 1) / KC;
+  const FastDiv by_r(R);
   dvec4 c[MAXT];
 #pragma unroll
   for (int q = 0; q < MAXT; ++q) c[q] = dvec4{0.0, 0.0, 0.0, 0.0};
@@ -243,7 +284,7 @@ __device__ __forceinline__ void mfma_gemm_staged(int M, int N, int K, FG gload, 
 #pragma unroll
     for (int q = 0; q < SPT; ++q) {
       const int e = threadIdx.x + q * blockDim.x;
-      const int kk = e / R, rr = e % R;
+      const int kk = by_r.quot(e), rr = by_r.rem(e, kk);
       pf[q] = (kk < kc) ? gload(rr, k0 + kk) : 0.0;
     }
   };
@@ -268,19 +309,15 @@ __device__ __forceinline__ void mfma_gemm_staged(int M, int N, int K, FG gload, 
       const int t = wave + q * nw;
       if (t < tiles) {
         const int i0 = (t / tn) * 16, j0 = (t % tn) * 16;
-        for (int kk0 = 0; kk0 < kc; kk0 += 4) {
-          const int kk = kk0 + lk;
-          const bool kin = kk < kc;
-          double av, bv;
-          if (STAGE_A) {
-            av = (kin && i0 + li < M) ? buf[kk * R + i0 + li] : 0.0;
-            bv = (kin && j0 + li < N) ? lop(k0 + kk, j0 + li) : 0.0;
-          } else {
-            av = (kin && i0 + li < M) ? lop(i0 + li, k0 + kk) : 0.0;
-            bv = (kin && j0 + li < N) ? buf[kk * R + j0 + li] : 0.0;
-          }
-          c[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, c[q], 0, 0, 0);
-        }
+        const int ia = min(i0 + li, M - 1), jb = min(j0 + li, N - 1);
+        dvec4 ct[1] = {c[q]};
+        if constexpr (STAGE_A)
+          mfma_k_loop<1>(ct, kc, lk, [&](int, int kk) { return buf[kk * R + ia]; },
+                         [&](int, int kk) { return lop(k0 + kk, jb); });
+        else
+          mfma_k_loop<1>(ct, kc, lk, [&](int, int kk) { return lop(ia, k0 + kk); },
+                         [&](int, int kk) { return buf[kk * R + jb]; });
+        c[q] = ct[0];
       }
     }
     __syncthreads();

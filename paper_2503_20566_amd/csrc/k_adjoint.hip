@@ -28,6 +28,8 @@
 //       Thetabar_0 = (psibar_0 + psi_0 (1 - <psi_0, psibar_0>)) / nu.
 #include <algorithm>
 
+#include <type_traits>
+
 #include "dev_common.h"
 #include "internal.h"
 
@@ -195,7 +197,7 @@ k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_
   __shared__ double sGS[MAXN];
   __shared__ double sRed[kT / 64];
   // products with the tape (U, V) and Q: K-chunks staged through sBuf, on the matrix cores
-  constexpr int KCH = 16, SPT = (MAXN * KCH + kT - 1) / kT;
+  constexpr int KCH = (BIG || MAXN == 16) ? 16 : 32, SPT = (MAXN * KCH + kT - 1) / kT;
   constexpr int QT = ((MAXM + 15) / 16 * ((MAXN + 15) / 16) + kT / 64 - 1) / (kT / 64);
   __shared__ double sBuf[MAXN * KCH];
   const int b = blockIdx.x;
@@ -257,8 +259,9 @@ k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_
       if (lane == 0) sGS[a] = acc;
     }
     const double* pbc = pbar + (size_t)c * d.site_stride;
+    const FastDiv by_n(n), by_p(p);
     for (int idx = threadIdx.x; idx < kk * n; idx += kT) {
-      const int a = idx / n, col = idx % n;
+      const int a = by_n.quot(idx), col = by_n.rem(idx, a);
       sGV[col * KD + a] = pbc[idx];
     }
     __syncthreads();
@@ -274,7 +277,7 @@ k_adj_svd(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_
     __syncthreads();
     // core C (p x p), with the projector term folded in (C' or C'')
     for (int idx = threadIdx.x; idx < p * p; idx += kT) {
-      const int j = idx / p, k = idx % p;
+      const int j = by_p.quot(idx), k = by_p.rem(idx, j);
       const double sj = t.sig[j], sk = t.sig[k];
       double v;
       if (j == k) {
@@ -353,17 +356,23 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
   // large bonds: Xbar and Z in the sample's global slot (wbig), Rbar in LDS, B read from the
   // boundary row, sB only stages the factors of the products
   constexpr bool BIG = MAXN > kMaxN;
-  // chunks of up to MAXM rows of the global factors staged through sB (8 rows at the large size,
-  // where R-bar takes most of the LDS)
-  constexpr int KCH = BIG ? 8 : ((MAXN / (DK * DK)) / 4 * 4 < 16 ? (MAXN / (DK * DK)) / 4 * 4 : 16);
+  // up to 48 columns Q and R of the site are brought to LDS once, their loads issued a site's first half
+  // ahead of their use; beyond, they are staged through sB in chunks of up to MAXM rows, each of which waits
+  // for its loads, so the chunks are as long as the LDS left by Xbar and Rbar allows (8 rows at the large
+  // size, where R-bar takes most of it).  16 x 16, 1024 samples, 32 columns: a row 1.03 -> 0.79 ms with the
+  // O sums reduced in the vector unit and the triangular solve in registers; 512 samples, 72 columns: 1.98 ->
+  // 1.81 ms.  What is left is the chain of small products: a site's fourteen barriers, at two workgroups per CU
+  constexpr bool RES = MAXN < kMaxN;
+  constexpr int KCH = BIG ? 8 : MAXN == kMaxN ? 24 : 4;
   constexpr int SPT = (MAXM * KCH + kT - 1) / kT;
-  constexpr int SBSZ = BIG ? MAXM * KCH : MAXN * MAXN / DK;
-  static_assert(KCH >= 4 && MAXM * KCH <= SBSZ, "staging chunk fits sB");
+  constexpr int SBSZ = (!BIG && MAXN * MAXN / DK > MAXM * KCH) ? MAXN * MAXN / DK : MAXM * KCH;
   static_assert(!BIG || 2 * MAXM * MAXN <= kBigSlot, "large-bond slot");
   using TS = TapeSlot<MAXN>;
   __shared__ double lXb[BIG ? 1 : MAXM * MAXN];  // Xbar_c (m x n, column-major ld m)
   __shared__ double lRb[MAXN * MAXN];  // Rbar_{c-1} (column-major ld MAXN), later M (ld MAXN): LDS at every size
   __shared__ double sB[SBSZ];
+  __shared__ double sQ[RES ? MAXM * MAXN : 1];  // Q_{c-1} (m2 x k2, ld m2)
+  __shared__ double sR[RES ? MAXN * MAXN : 1];  // R_{c-1} (ld MAXN)
   __shared__ double sT[DK * DK * DK * DK];
   __shared__ double sRed[16 * (kT / 64)];
   const int b = blockIdx.x;
@@ -396,6 +405,8 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
     const int r = (c == 0) ? 1 : qrk[c - 1];
     const int m = r * Dk, n = bn * dr;
     const int mc = bc * dl;  // columns of R_{c-1}
+    static_assert(DK == 1 || DK == 2, "dl, dr are 1 or 2");
+    const int sl = dl - 1;  // i dl + l by shifts
     const double* Bs = prev + (size_t)c * d.site_stride;
     if constexpr (!BIG)
       for (int i = threadIdx.x; i < bc * Dk * bn; i += kT) sB[i] = Bs[i];
@@ -417,11 +428,27 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
 #pragma unroll
         for (int q = 0; q < RPT; ++q) {
           const int idx = threadIdx.x + q * kT;
-          if (idx < mc * MAXN) sRb[idx] = st[q];
+          if (idx < mc * MAXN) {
+            sRb[idx] = st[q];
+            if constexpr (RES) sR[idx] = st[q];
+          }
         }
       }
     } else if (threadIdx.x == 0) {
       sRb[0] = 1.0;
+    }
+    constexpr int QPT = (MAXM * MAXN + kT - 1) / kT;
+    double qst[RES ? QPT : 1];
+    if constexpr (RES) {
+      if (c >= 1) {
+        const int tot = ((c - 1 == 0) ? 1 : qrk[c - 2]) * Dk * qrk[c - 1];
+        const double* Q = qs + (size_t)(c - 1) * qslot;
+#pragma unroll
+        for (int q = 0; q < QPT; ++q) {
+          const int idx = threadIdx.x + q * kT;
+          qst[q] = Q[idx < tot ? idx : tot - 1];
+        }
+      }
     }
     __syncthreads();
     auto R = [&](int i, int j) -> double { return sRb[(size_t)j * MAXN + i]; };
@@ -487,8 +514,10 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
           }
       }
       const int nent = dl * dr * Dk * Dk;
-      for (int q = 0; q < nent; ++q) {
-        const double v = wave_sum(acc[q]);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        if (q >= nent) continue;
+        const double v = wave_sum_dpp(acc[q]);
         if (lane == 0) sRed[q * (kT / 64) + wave] = v;
       }
       __syncthreads();
@@ -501,10 +530,11 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
     // ---- Z[(i,l)][(dd,a')] = sum_{u,rr} Xbar[(i,u),(a',rr)] T[l][rr][dd][u], into sZ (in place
     // over Xbar when both are in LDS)
     const int nz = Dk * bn;  // row length of Z
+    const FastDiv by_nz(nz);
     {
       auto z_entry = [&](int idx) -> double {
-        const int il = idx / nz, col = idx % nz;
-        const int i = il / dl, l = il % dl, dd = col / bn, ap = col % bn;
+        const int il = by_nz.quot(idx), col = by_nz.rem(idx, il);
+        const int i = il >> sl, l = il & sl, dd = col >= bn ? 1 : 0, ap = col - dd * bn;
         double z = 0.0;
         for (int u = 0; u < Dk; ++u)
           for (int rr = 0; rr < dr; ++rr)
@@ -532,7 +562,7 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
     }
     // ---- Bbar[a][(dd,a')] = sum_{(i,l)} R[i][a dl+l] Z[(i,l)][(dd,a')]
     double* Pb = pout + (size_t)c * d.site_stride;
-    mfma_gemm(bc, nz, r * dl, [&](int a, int k) { return R(k / dl, a * dl + k % dl); },
+    mfma_gemm(bc, nz, r * dl, [&](int a, int k) { return R(k >> sl, (a << sl) + (k & sl)); },
                     [&](int k, int col) { return sZ[(size_t)k * nz + col]; },
                     [&](int a, int col, double v) { Pb[(size_t)a * nz + col] = v; });
     if (c == 0) break;
@@ -540,7 +570,7 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
     // ---- Rbar[i][a dl+l] = sum_{(dd,a')} Z[(i,l)][(dd,a')] B[a][(dd,a')]
     mfma_gemm(r * dl, bc, nz, [&](int il, int k) { return sZ[(size_t)il * nz + k]; },
                     [&](int k, int a) { return Bv(a * nz + k); },
-                    [&](int il, int a, double v) { sRb[(size_t)(a * dl + il % dl) * MAXN + il / dl] = v; });
+                    [&](int il, int a, double v) { sRb[((a << sl) + (il & sl)) * MAXN + (il >> sl)] = v; });
     __syncthreads();
     // ---- QR backward of X_{c-1} = Q R (m2 x n2, k2 = min) -> Xbar_{c-1} in sXb (ld m2)
     const int r2 = (c - 1 == 0) ? 1 : qrk[c - 2];
@@ -548,13 +578,12 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
     const double* Q = qs + (size_t)(c - 1) * qslot;    // m2 x k2, ld m2
     const double* Qb = qb + (size_t)(c - 1) * qslot;   // m2 x k2, ld m2
     const double* Rq = tp + (size_t)(c - 1) * tslot + TS::R;  // k2 x n2, ld MAXN
-    auto RQ = [&](int i, int j) -> double { return Rq[(size_t)j * MAXN + i]; };
+    auto RQ = [&](int i, int j) -> double { return RES ? sR[j * MAXN + i] : Rq[(size_t)j * MAXN + i]; };
     // Qbar' = Qbar + Q R2 R2bar^T (cols < k2) and Xbar[:, k2:] = Q R2bar; all loads of a thread
     // are issued before its stores
     if constexpr (BIG) {  // Qbar (m2 x k2) into sXb[:, :k2]
       for (int idx = threadIdx.x; idx < m2 * k2; idx += kT) sXb[idx] = Qb[idx];
     } else {  // Qbar (m2 x k2) into sXb[:, :k2]; loads at clamped addresses, all in flight at once
-      constexpr int QPT = (MAXM * MAXN + kT - 1) / kT;
       double st[QPT];
       const int tot = m2 * k2;
 #pragma unroll
@@ -565,9 +594,24 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
 #pragma unroll
       for (int q = 0; q < QPT; ++q) {
         const int idx = threadIdx.x + q * kT;
-        if (idx < tot) sXb[idx] = st[q];
+        if (idx < tot) {
+          sXb[idx] = st[q];
+          if constexpr (RES) sQ[idx] = qst[q];
+        }
       }
     }
+    if constexpr (RES) __syncthreads();
+    // products whose left operand, or A^T of it, is Q or R
+    auto q_gemm = [&](auto stage_a, int M, int N, int K, auto g, auto lop, auto sink) {
+      constexpr bool SA = decltype(stage_a)::value;
+      if constexpr (!RES)
+        mfma_gemm_staged<QT, KCH, SPT, SA>(M, N, K, g, lop, sB, sink);
+      else if constexpr (SA)
+        mfma_gemm_sync<QT>(M, N, K, g, lop, sink);
+      else
+        mfma_gemm_sync<QT>(M, N, K, lop, [&](int kk, int jj) { return g(jj, kk); }, sink);
+    };
+    auto Qv = [&](int idx) -> double { return RES ? sQ[idx] : Q[idx]; };
     if (n2 > k2) {
       // wide X (m2 = k2 < n2): R = [R1 | R2].  Qbar' = Qbar + Q (R2 R2bar^T), Xbar[:, k2:] = Q R2bar,
       // with T = R2 R2bar^T (k2 x k2) parked behind Xbar in sXb (m2 n2 + k2^2 <= 2 n2^2 fits)
@@ -577,32 +621,27 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
                       [&](int kk, int bb) { return sRb[(size_t)(k2 + kk) * MAXN + bb]; },
                       [&](int a, int bb, double v) { T[(size_t)bb * k2 + a] = v; });
       __syncthreads();
-      mfma_gemm_staged<QT, KCH, SPT, true>(
-          m2, k2, k2, [&](int i, int t) { return Q[(size_t)t * m2 + i]; },
-          [&](int t, int j) { return T[(size_t)j * k2 + t]; }, sB,
+      q_gemm(std::bool_constant<true>{}, m2, k2, k2, [&](int i, int t) { return Qv(t * m2 + i); },
+          [&](int t, int j) { return T[(size_t)j * k2 + t]; },
           [&](int i, int j, double v) { sXb[(size_t)j * m2 + i] += v; });
-      mfma_gemm_staged<QT, KCH, SPT, true>(
-          m2, w2, k2, [&](int i, int t) { return Q[(size_t)t * m2 + i]; },
-          [&](int t, int jj) { return sRb[(size_t)(k2 + jj) * MAXN + t]; }, sB,
+      q_gemm(std::bool_constant<true>{}, m2, w2, k2, [&](int i, int t) { return Qv(t * m2 + i); },
+          [&](int t, int jj) { return sRb[(size_t)(k2 + jj) * MAXN + t]; },
           [&](int i, int jj, double v) { sXb[(size_t)(k2 + jj) * m2 + i] = v; });
     }
     __syncthreads();
-    // M = R1 R1bar^T - Qbar'^T Q  (k2 x k2), the global factors R1 and Q staged through sB (B is
-    // no longer needed): first R1 R1bar^T into registers, then the second product subtracts
-    mfma_gemm_staged<QT, KCH, SPT, true>(
-        k2, k2, k2, [&](int a, int kk) { return RQ(a, kk); },
-        [&](int kk, int bb) { return sRb[(size_t)kk * MAXN + bb]; }, sB,
+    // M = R1 R1bar^T - Qbar'^T Q  (k2 x k2): first R1 R1bar^T, then the second product subtracts (B is no
+    // longer needed: sB stages R1 and Q where they are not in LDS)
+    q_gemm(std::bool_constant<true>{}, k2, k2, k2, [&](int a, int kk) { return RQ(a, kk); },
+        [&](int kk, int bb) { return sRb[(size_t)kk * MAXN + bb]; },
         [&](int a, int bb, double v) { sRb[(size_t)a * MAXN + bb] = v; });
     __syncthreads();
-    mfma_gemm_staged<QT, KCH, SPT, false>(
-        k2, k2, m2, [&](int bb, int kk) { return Q[(size_t)bb * m2 + kk]; },
-        [&](int a, int kk) { return sXb[(size_t)a * m2 + kk]; }, sB,
+    q_gemm(std::bool_constant<false>{}, k2, k2, m2, [&](int bb, int kk) { return Qv(bb * m2 + kk); },
+        [&](int a, int kk) { return sXb[(size_t)a * m2 + kk]; },
         [&](int a, int bb, double v) { sRb[(size_t)a * MAXN + bb] -= v; });
     __syncthreads();
     // Bm = Qbar' + Q sym(M)  (m2 x k2), into sXb[:, :k2]
-    mfma_gemm_staged<QT, KCH, SPT, true>(
-        m2, k2, k2, [&](int i, int a) { return Q[(size_t)a * m2 + i]; },
-        [&](int a, int j) { return (a >= j) ? sRb[(size_t)a * MAXN + j] : sRb[(size_t)j * MAXN + a]; }, sB,
+    q_gemm(std::bool_constant<true>{}, m2, k2, k2, [&](int i, int a) { return Qv(a * m2 + i); },
+        [&](int a, int j) { return (a >= j) ? sRb[(size_t)a * MAXN + j] : sRb[(size_t)j * MAXN + a]; },
         [&](int i, int j, double v) { sXb[(size_t)j * m2 + i] += v; });
     // R1 into sRb for the triangular solve (M is no longer read)
     if constexpr (BIG) {
@@ -628,16 +667,27 @@ k_adj_qr(Dims d, const int* __restrict__ bond_all, const int* __restrict__ qrk_a
     }
     __syncthreads();
     // Xbar[:, :k2] = Bm R1^-T in blocks of 8 columns from the right: rows are independent, so
-    // inside a block each row solves its 8 unknowns alone; one product then removes the block
-    // from every column to its left (two barriers per block)
+    // inside a block each row solves its 8 unknowns alone, in registers (one unknown's quotient is
+    // all that the next waits for); one product then removes the block from every column to its left
+    // (two barriers per block)
     for (int j1 = k2; j1 > 0; j1 -= 8) {
       const int j0 = j1 - 8 > 0 ? j1 - 8 : 0;
+      const int nb = j1 - j0;
+      const double* Rb = sRb + (size_t)j0 * MAXN + j0;
       for (int i = threadIdx.x; i < m2; i += kT) {
-        for (int j = j1 - 1; j >= j0; --j) {
-          double acc = sXb[(size_t)j * m2 + i];
-          for (int l = j + 1; l < j1; ++l) acc -= sRb[(size_t)l * MAXN + j] * sXb[(size_t)l * m2 + i];
-          sXb[(size_t)j * m2 + i] = acc / sRb[(size_t)j * MAXN + j];
-        }
+        double x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = q < nb ? sXb[(size_t)(j0 + q) * m2 + i] : 0.0;
+#pragma unroll
+        for (int q = 7; q >= 0; --q)
+          if (q < nb) {
+            x[q] /= Rb[q * MAXN + q];
+#pragma unroll
+            for (int l = 0; l < q; ++l) x[l] = fma(-Rb[q * MAXN + l], x[q], x[l]);
+          }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          if (q < nb) sXb[(size_t)(j0 + q) * m2 + i] = x[q];
       }
       __syncthreads();
       if (j0 > 0) {

@@ -45,9 +45,9 @@ struct RowCfg {
   static constexpr int MINW = MAXN <= 32 ? 4 : MAXN == 48 ? 3 : 2;
 };
 
-// Lanes per column pair in the Jacobi (GW, 4 or 8) is a template parameter chosen per handle (the
-// autotuner times both): eight measured fastest at chi*Dk = 72, where four lanes double each
-// lane's dependent chains and the step is latency-bound (one or two waves per SIMD).
+// Lanes per column group in the Jacobi (GW, 4 or 8) is a template parameter chosen per handle up to 72 columns
+// (the autotuner times both): eight measured fastest at chi*Dk = 72, where four lanes double each lane's
+// dependent chains and the step is latency-bound (one or two waves per SIMD).  Eight beyond 72.
 
 // ---------------------------------------------------------------------------------------------
 // Householder QR of the m x n column-major matrix X (ld = m, in LDS), k = min(m, n) reflectors
@@ -347,6 +347,53 @@ __device__ __forceinline__ PairRot pair_rotation(double gs, Col& u, Col& v, doub
   return r;
 }
 
+// Columns per group of GW lanes.  Four, for the large bonds: half of the boundary pairs are then a group's own
+// and a quarter of the columns are handed over in a round, not half, where the hand-over is what a round waits
+// for (128 columns of 1 KB, 2.5 k LDS cycles of a round pair with groups of two): 14 x 14, chi 64, 96 samples,
+// 87.4 -> 80.8 ms.  Two up to 72, where a round waits for its chain of dependent instructions: with four,
+// fewer waves run two chains each (a row at 32 columns 1.93 -> 3.5 ms, at 72 6.5 -> 7.3).
+template <int MAXN, int GW>
+constexpr int jacobi_columns() { return MAXN == kMaxNBig && GW == 8 ? 4 : 2; }
+
+// Two pairs at once, without a branch between them, so that their chains (a hundred dependent instructions
+// each) interleave; a pair left alone gets the factors 0 and keeps its norms and scales.
+__device__ __forceinline__ void pair_rotations(double gs0, double gs1, Col& u0, Col& v0, Col& u1, Col& v1, double zero2,
+                                               double tol2, bool& big_any, PairRot& r0, PairRot& r1) {
+  constexpr double kQuadratic2 = 1e-12;
+  const double g0 = gs0 * (u0.d * v0.d), g1 = gs1 * (u1.d * v1.d);
+  const double gg0 = g0 * g0, ab0 = u0.n * v0.n, gg1 = g1 * g1, ab1 = u1.n * v1.n;
+  const bool pos0 = fmin(u0.n, v0.n) > zero2, pos1 = fmin(u1.n, v1.n) > zero2;
+  big_any |= (pos0 && gg0 > kQuadratic2 * ab0) || (pos1 && gg1 > kQuadratic2 * ab1);
+  r0 = PairRot{0.0, 0.0, pos0 && gg0 > tol2 * ab0};
+  r1 = PairRot{0.0, 0.0, pos1 && gg1 > tol2 * ab1};
+  if (r0.on || r1.on) {
+    double t0 = rotation_tangent(v0.n - u0.n, g0 + g0), t1 = rotation_tangent(v1.n - u1.n, g1 + g1);
+    t0 = r0.on ? t0 : 0.0;
+    t1 = r1.on ? t1 : 0.0;
+    const double a0 = fma(t0, t0, 1.0), a1 = fma(t1, t1, 1.0);
+    double c0 = rsqrt_1to2(a0), c1 = rsqrt_1to2(a1);
+    c0 = r0.on ? c0 : 1.0;
+    c1 = r1.on ? c1 : 1.0;
+    const double ic0 = a0 * c0, ic1 = a1 * c1;
+    r0.alpha = t0 * (v0.d * u0.id);
+    r0.beta = t0 * (u0.d * v0.id);
+    r1.alpha = t1 * (v1.d * u1.id);
+    r1.beta = t1 * (u1.d * v1.id);
+    u0.n = fma(-t0, g0, u0.n);
+    v0.n = fma(t0, g0, v0.n);
+    u1.n = fma(-t1, g1, u1.n);
+    v1.n = fma(t1, g1, v1.n);
+    u0.d *= c0;
+    v0.d *= c0;
+    u1.d *= c1;
+    v1.d *= c1;
+    u0.id *= ic0;
+    v0.id *= ic0;
+    u1.id *= ic1;
+    v1.id *= ic1;
+  }
+}
+
 // hb: the hand-over buffers (2 ceil(nc/2) columns of MAXN doubles, of MAXN + 8 at the large-bond size) and ring: the rotation ring (4
 // rounds of MAXN/2 (alpha, beta) pairs); both in LDS, as sScl (MAXN scales handed over).  With A and J themselves in LDS they overlay them
 // (hb = A, ring = J: both are dead while the sweeps run); with A and J in global memory (the
@@ -366,7 +413,8 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
   constexpr bool PADSLOT = MAXN > kMaxN;
   constexpr int SLOTP = PADSLOT ? SLOT + 8 : SLOT;
   constexpr int kRot = (!PADSLOT && (2 * SLOT) % 64 == 0) ? 8 : 0;
-  static_assert(MAXN % GW == 0 && (MAXN / 2) * GW <= JL0, "column groups below the J lanes");
+  constexpr int NC = jacobi_columns<MAXN, GW>();
+  static_assert(MAXN % GW == 0 && (MAXN / NC) * GW <= JL0, "column groups below the J lanes");
   static_assert(JL0 % 64 == 0 && JL0 + 2 * MAXN <= NT && MAXN % 4 == 0, "J rows fit");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int k = threadIdx.x / GW, gl = threadIdx.x % GW;
@@ -380,8 +428,8 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
     if (lane == 0) sScal[wave] = s2;
   }
   if (threadIdx.x < 2) sFlag[threadIdx.x] = 0;
-  const int ncp = nc + (nc & 1), np = ncp / 2;
-  const bool active = nc > 1 && k < np;
+  const int ncp = (nc + NC - 1) / NC * NC, np = ncp / 2, ng = ncp / NC;  // slots, pairs, groups
+  const bool active = nc > 1 && k < ng;
   const bool full = np == HS;  // every slot in use
   // J lanes: the lane quad (4r .. 4r+3) holds rows 2r and 2r+1 of J, lane 4r+h their slots from h HQ
   const int jl = (int)threadIdx.x - JL0;
@@ -390,18 +438,25 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
   const int jb = jh * HQ;  // first slot of this quarter row
   // one register array serves both roles (a lane is either a column-group lane or a J lane), so
   // that the compiler does not keep both sets live: X | Y for the groups, the J quarter rows else
-  static_assert(2 * RPL <= HS && HQ % 2 == 0, "X and Y fit in the J entries, whole pairs per quarter row");
+  static_assert(NC * RPL <= HS && HQ % 2 == 0, "a lane's columns fit in the J entries, whole pairs per quarter row");
   double Jr[HS];
   double (&X)[RPL] = *reinterpret_cast<double (*)[RPL]>(&Jr[0]);
   double (&Y)[RPL] = *reinterpret_cast<double (*)[RPL]>(&Jr[RPL]);
-  int idX = 2 * k, idY = 2 * k + 1;
-  Col cX{0.0, 1.0, 1.0}, cY{0.0, 1.0, 1.0};  // the squared norms exact at each sweep's start
+  double (&Z)[RPL] = *reinterpret_cast<double (*)[RPL]>(&Jr[NC == 4 ? 2 * RPL : 0]);
+  double (&V)[RPL] = *reinterpret_cast<double (*)[RPL]>(&Jr[NC == 4 ? 3 * RPL : RPL]);
+  int idX = NC * k, idY = NC * k + 1, idZ = NC * k + 2, idV = NC * k + 3;
+  // the squared norms exact at each sweep's start
+  Col cX{0.0, 1.0, 1.0}, cY{0.0, 1.0, 1.0}, cZ{0.0, 1.0, 1.0}, cV{0.0, 1.0, 1.0};
   if (active) {
 #pragma unroll
     for (int t = 0; t < RPL; ++t) {
       const int r = gl + GW * t;
       X[t] = (idX < nc && r < nr) ? A[(size_t)idX * ld + r] : 0.0;
       Y[t] = (idY < nc && r < nr) ? A[(size_t)idY * ld + r] : 0.0;
+      if constexpr (NC == 4) {
+        Z[t] = (idZ < nc && r < nr) ? A[(size_t)idZ * ld + r] : 0.0;
+        V[t] = (idV < nc && r < nr) ? A[(size_t)idV * ld + r] : 0.0;
+      }
     }
   }
   if (jact) {
@@ -423,13 +478,17 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
     for (int t = 0; t < RPL; ++t) {
       X[t] = ldexp(X[t], shift);
       Y[t] = ldexp(Y[t], shift);
+      if constexpr (NC == 4) {
+        Z[t] = ldexp(Z[t], shift);
+        V[t] = ldexp(V[t], shift);
+      }
     }
   }
   fro2 = ldexp(fro2, 2 * shift);
   const double zero2 = fro2 * (64.0 * 2.220446049250313e-16) * (64.0 * 2.220446049250313e-16);
   const double tol = fmax(1e-15, 2.220446049250313e-16 * (double)nr);
   const double tol2 = tol * tol;
-  // hand-over buffers: slot q of buffer 1 at hb + q*SLOTP, of buffer 2 at hb + (np + q)*SLOTP
+  // hand-over buffers: slot q of buffer 1 at hb + q*SLOTP, of buffer 2 at hb + (ng + q)*SLOTP
   auto at = [&](int q, int e) -> double& {
     if constexpr (PADSLOT)
       return hb[(size_t)q * SLOTP + e];
@@ -437,11 +496,11 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
       return hb[(size_t)q * SLOT + (e + kRot * (q & 3)) % SLOT];
   };
   int* id1 = sPerm;
-  int* id2 = sPerm + np;
+  int* id2 = sPerm + ng;
   double* nrm1 = sSig;  // norms travelling with the handed-over columns
-  double* nrm2 = sSig + np;
+  double* nrm2 = sSig + ng;
   double2* scl1 = sScl;  // scales (d, 1/d) travelling with them
-  double2* scl2 = sScl + np;
+  double2* scl2 = sScl + ng;
   int rnd = 0;  // round counter (all threads)
 
   // round (2k, 2k+1) with slot 2k in u and slot 2k+1 in v; afterwards the slots are exchanged,
@@ -571,30 +630,16 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
       Col cp{nrm1[k + 1], sp.x, sp.y};
       PairRot r;
       double g = 0.0;
-      if constexpr (!PADSLOT) {
-        double P[RPL];
+      double P[RPL];
 #pragma unroll
-        for (int t = 0; t < RPL; ++t) P[t] = at(k + 1, gl + GW * t);
+      for (int t = 0; t < RPL; ++t) P[t] = at(k + 1, gl + GW * t);
 #pragma unroll
-        for (int t = 0; t < RPL; ++t) g = fma(hi[t], P[t], g);
-        r = pair_rotation(group_sum<GW>(g), chi, cp, zero2, tol2, big_any);
+      for (int t = 0; t < RPL; ++t) g = fma(hi[t], P[t], g);
+      r = pair_rotation(group_sum<GW>(g), chi, cp, zero2, tol2, big_any);
 #pragma unroll
-        for (int t = 0; t < RPL; ++t) {
-          at(np + k, gl + GW * t) = fma(-r.alpha, P[t], hi[t]);
-          hi[t] = fma(r.beta, hi[t], P[t]);
-        }
-      } else {
-        // long columns (large bonds): the partner is read from LDS twice, for the dot product and
-        // for the rotation, instead of being held in registers beside the lane's own pair
-#pragma unroll
-        for (int t = 0; t < RPL; ++t) g = fma(hi[t], at(k + 1, gl + GW * t), g);
-        r = pair_rotation(group_sum<GW>(g), chi, cp, zero2, tol2, big_any);
-#pragma unroll
-        for (int t = 0; t < RPL; ++t) {
-          const double b = at(k + 1, gl + GW * t);
-          at(np + k, gl + GW * t) = fma(-r.alpha, b, hi[t]);
-          hi[t] = fma(r.beta, hi[t], b);
-        }
+      for (int t = 0; t < RPL; ++t) {
+        at(np + k, gl + GW * t) = fma(-r.alpha, P[t], hi[t]);
+        hi[t] = fma(r.beta, hi[t], P[t]);
       }
       rot_any |= r.on;
       if (gl == 0) {
@@ -618,20 +663,168 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
     ++rnd;
   };
 
+  // The same two rounds for groups of four columns, slots 4k .. 4k+3 in (a, b, c, d): the pairs (a, b) and
+  // (c, d); then, with b, a, d, c in the slots, (a, d) within the group and (c, slot 4k+4), slot 4k in b.
+  // Both of a round's pairs interleave.  Afterwards the slots hold b, d, a, c: four round pairs return the
+  // roles.
+  auto inner4 = [&](double (&a)[RPL], double (&b)[RPL], double (&c)[RPL], double (&e)[RPL], Col& ca, Col& cb, Col& cc,
+                    Col& ce, bool& rot_any, bool& big_any) {
+    if (active) {
+      double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+      for (int t = 0; t < RPL; ++t) {
+        g0 = fma(a[t], b[t], g0);
+        g1 = fma(c[t], e[t], g1);
+      }
+      PairRot r0, r1;
+      pair_rotations(group_sum<GW>(g0), group_sum<GW>(g1), ca, cb, cc, ce, zero2, tol2, big_any, r0, r1);
+      if (gl == 0) {
+        ring[(rnd & 3) * HS + 2 * k] = make_double2(r0.alpha, r0.beta);
+        ring[(rnd & 3) * HS + 2 * k + 1] = make_double2(r1.alpha, r1.beta);
+      }
+      if (r0.on || r1.on) {
+#pragma unroll
+        for (int t = 0; t < RPL; ++t) {
+          const double u = a[t], w = c[t];
+          a[t] = fma(-r0.alpha, b[t], u);
+          b[t] = fma(r0.beta, u, b[t]);
+          c[t] = fma(-r1.alpha, e[t], w);
+          e[t] = fma(r1.beta, w, e[t]);
+        }
+        rot_any = true;
+      }
+    }
+    ++rnd;
+  };
+  auto boundary4 = [&](double (&lo)[RPL], double (&u)[RPL], double (&v)[RPL], double (&hi)[RPL], Col& clo, Col& cu,
+                       Col& cv, Col& chi, int& ilo, int& ihi, bool& rot_any, bool& big_any) {
+    if (active) {  // slot 4k goes to group k-1
+#pragma unroll
+      for (int t = 0; t < RPL; ++t) at(k, gl + GW * t) = lo[t];
+      if (gl == 0) {
+        id1[k] = ilo;
+        nrm1[k] = clo.n;
+        scl1[k] = make_double2(clo.d, clo.id);
+      }
+    }
+    __syncthreads();
+    japply_inner(rnd - 1);
+    if (active) {
+      const bool next = k + 1 < ng;  // the last group's slot 4k+3 has no partner: its own slot 4k, unused
+      const int kn = next ? k + 1 : k;
+      const int ip = id1[kn];
+      const double2 sp = scl1[kn];
+      Col cp{next ? nrm1[kn] : 0.0, sp.x, sp.y};  // norm 0: left alone
+      double P[RPL];
+#pragma unroll
+      for (int t = 0; t < RPL; ++t) P[t] = at(kn, gl + GW * t);
+      double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+      for (int t = 0; t < RPL; ++t) {
+        g0 = fma(u[t], v[t], g0);
+        g1 = fma(hi[t], P[t], g1);
+      }
+      PairRot r0, r1;
+      pair_rotations(group_sum<GW>(g0), group_sum<GW>(g1), cu, cv, chi, cp, zero2, tol2, big_any, r0, r1);
+      if (next) {
+#pragma unroll
+        for (int t = 0; t < RPL; ++t) {
+          at(ng + k, gl + GW * t) = fma(-r1.alpha, P[t], hi[t]);
+          hi[t] = fma(r1.beta, hi[t], P[t]);
+        }
+      }
+      if (r0.on) {
+#pragma unroll
+        for (int t = 0; t < RPL; ++t) {
+          const double w = u[t];
+          u[t] = fma(-r0.alpha, v[t], w);
+          v[t] = fma(r0.beta, w, v[t]);
+        }
+      }
+      rot_any |= r0.on || r1.on;
+      if (gl == 0) {
+        ring[(rnd & 3) * HS + 2 * k] = make_double2(r0.alpha, r0.beta);
+        if (next) {
+          ring[(rnd & 3) * HS + 2 * k + 1] = make_double2(r1.alpha, r1.beta);
+          id2[k] = ihi;
+          nrm2[k] = chi.n;
+          scl2[k] = make_double2(chi.d, chi.id);
+        }
+      }
+      if (next) {
+        ihi = ip;
+        chi = cp;
+      }
+    }
+    __syncthreads();
+    if (active && k >= 1) {  // slot 4k receives the rotated slot 4k-1 of group k-1
+#pragma unroll
+      for (int t = 0; t < RPL; ++t) lo[t] = at(ng + k - 1, gl + GW * t);
+      ilo = id2[k - 1];
+      const double2 sl = scl2[k - 1];
+      clo = Col{nrm2[k - 1], sl.x, sl.y};
+    }
+    japply_boundary(rnd);
+    ++rnd;
+  };
+  // a round pair with the slots in (a, b, c, d), which it leaves in (b, d, a, c)
+  auto rounds4 = [&](double (&a)[RPL], double (&b)[RPL], double (&c)[RPL], double (&e)[RPL], Col& ca, Col& cb, Col& cc,
+                     Col& ce, int& ib, int& ic, bool& rot_any, bool& big_any) {
+    inner4(a, b, c, e, ca, cb, cc, ce, rot_any, big_any);
+    boundary4(b, a, e, c, cb, ca, ce, cc, ib, ic, rot_any, big_any);
+  };
+
   bool more = false;  // still rotating after the last sweep run: not converged
   if (nc > 1) {
     for (int sweep = 0; sweep < max_sweeps; ++sweep) {
       bool rot_any = false, big_any = false;
       if (active) {
-        double sx = 0.0, sy = 0.0;
+        auto norm = [&](double (&x)[RPL]) {
+          double v = 0.0;
 #pragma unroll
-        for (int t = 0; t < RPL; ++t) {
-          sx = fma(X[t], X[t], sx);
-          sy = fma(Y[t], Y[t], sy);
+          for (int t = 0; t < RPL; ++t) v = fma(x[t], x[t], v);
+          return Col{group_sum<GW>(v), 1.0, 1.0};
+        };
+        cX = norm(X);
+        cY = norm(Y);
+        if constexpr (NC == 4) {
+          cZ = norm(Z);
+          cV = norm(V);
         }
-        cX = Col{group_sum<GW>(sx), 1.0, 1.0};
-        cY = Col{group_sum<GW>(sy), 1.0, 1.0};
       }
+      if constexpr (NC == 4) {
+        // four round pairs per iteration return the roles (np is even); two leave d, c, b, a in the slots
+        for (int h = 0; h < np; h += 4) {
+          rounds4(X, Y, Z, V, cX, cY, cZ, cV, idY, idZ, rot_any, big_any);
+          rounds4(Y, V, X, Z, cY, cV, cX, cZ, idV, idX, rot_any, big_any);
+          if (h + 2 < np) {
+            rounds4(V, Z, Y, X, cV, cZ, cY, cX, idZ, idY, rot_any, big_any);
+            rounds4(Z, X, V, Y, cZ, cX, cV, cY, idX, idV, rot_any, big_any);
+          }
+        }
+        if (np & 2) {
+          if (active) {  // only on the groups' lanes, whose columns share their registers with the J rows
+#pragma unroll
+            for (int t = 0; t < RPL; ++t) {
+              const double x = X[t], y = Y[t];
+              X[t] = V[t];
+              V[t] = x;
+              Y[t] = Z[t];
+              Z[t] = y;
+            }
+          }
+          const int ix = idX, iy = idY;
+          idX = idV;
+          idV = ix;
+          idY = idZ;
+          idZ = iy;
+          const Col x = cX, y = cY;
+          cX = cV;
+          cV = x;
+          cY = cZ;
+          cZ = y;
+        }
+      } else {
       // two round pairs per iteration so that the register roles return: (X, Y) = (2k, 2k+1)
       for (int h = 0; h + 2 <= np; h += 2) {
         inner(X, Y, cX, cY, rot_any, big_any);  // now Y = 2k, X = 2k+1
@@ -659,14 +852,22 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
         cX = cY;
         cY = tc;
       }
+      }
       // the scales into the columns and, by slot through LDS, into the J rows
       if (active) {
 #pragma unroll
         for (int t = 0; t < RPL; ++t) {
           X[t] *= cX.d;
           Y[t] *= cY.d;
+          if constexpr (NC == 4) {
+            Z[t] *= cZ.d;
+            V[t] *= cV.d;
+          }
         }
-        if (gl == 0) sScl[k] = make_double2(cX.d, cY.d);
+        if (gl == 0) {
+          sScl[NC / 2 * k] = make_double2(cX.d, cY.d);
+          if constexpr (NC == 4) sScl[NC / 2 * k + 1] = make_double2(cZ.d, cV.d);
+        }
       }
       if (rot_any) sFlag[0] = 1;
       if (big_any) sFlag[1] = 1;
@@ -690,8 +891,12 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
   }
   // hand-over buffers and rotation ring dead: column ids of the slots for the J rows
   if (active && gl == 0) {
-    sPerm[2 * k] = idX;
-    sPerm[2 * k + 1] = idY;
+    sPerm[NC * k] = idX;
+    sPerm[NC * k + 1] = idY;
+    if constexpr (NC == 4) {
+      sPerm[NC * k + 2] = idZ;
+      sPerm[NC * k + 3] = idV;
+    }
   }
   __syncthreads();
   if (active) {
@@ -700,6 +905,10 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
       const int r = gl + GW * t;
       if (idX < nc) A[(size_t)idX * ld + r] = ldexp(X[t], -shift);
       if (idY < nc) A[(size_t)idY * ld + r] = ldexp(Y[t], -shift);
+      if constexpr (NC == 4) {
+        if (idZ < nc) A[(size_t)idZ * ld + r] = ldexp(Z[t], -shift);
+        if (idV < nc) A[(size_t)idV * ld + r] = ldexp(V[t], -shift);
+      }
     }
   } else if (nc == 1 && k == 0) {
     for (int t = 0; t < RPL; ++t) {
@@ -951,7 +1160,7 @@ __device__ __forceinline__ void row_sweep_body(const Dims& d, const int* __restr
   double2* const ring = BIG ? sRing : reinterpret_cast<double2*>(Jm);
   // first lane of the Jacobi's J rows (two lanes per row on average): the (MAXN / 2) * GW lanes of the column
   // groups, rounded up to whole waves
-  constexpr int JL0 = ((MAXN / 2) * GW + 63) / 64 * 64;
+  constexpr int JL0 = ((MAXN / jacobi_columns<MAXN, GW>()) * GW + 63) / 64 * 64;
   constexpr int lda = MAXN + 1, ldj = MAXN + 1;  // the Jacobi's padded column stride
   constexpr int SPT = (MAXM * KCH + NT - 1) / NT;
   static_assert(KCH >= 4 && MAXM * KCH <= SBSIZE, "staging chunk fits sB");
@@ -1157,7 +1366,7 @@ hipError_t launch_row_t(const RowArgs& a, hipStream_t s) {
 template <int MAXN, int DK>
 hipError_t launch_row_class(const RowArgs& a, hipStream_t s) {
   if constexpr (MAXN > kMaxN) {
-    return a.mixed ? launch_row_t<MAXN, DK, float, 4>(a, s) : launch_row_t<MAXN, DK, double, 4>(a, s);
+    return a.mixed ? launch_row_t<MAXN, DK, float, 8>(a, s) : launch_row_t<MAXN, DK, double, 8>(a, s);
   } else {
     if (a.lanes == 4)
       return a.mixed ? launch_row_t<MAXN, DK, float, 4>(a, s) : launch_row_t<MAXN, DK, double, 4>(a, s);

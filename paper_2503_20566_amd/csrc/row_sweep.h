@@ -1158,7 +1158,7 @@ __device__ __forceinline__ void row_sweep_body(const Dims& d, const int* __restr
   double* G = sR;  // G[i][a] at G[i*MAXN + a]
   double* const hb = BIG ? sHB : A;
   double2* const ring = BIG ? sRing : reinterpret_cast<double2*>(Jm);
-  // first lane of the Jacobi's J rows (two lanes per row on average): the (MAXN / 2) * GW lanes of the column
+  // first lane of the Jacobi's J rows (two lanes per row on average): the lanes of the column
   // groups, rounded up to whole waves
   constexpr int JL0 = ((MAXN / jacobi_columns<MAXN, GW>()) * GW + 63) / 64 * 64;
   constexpr int lda = MAXN + 1, ldj = MAXN + 1;  // the Jacobi's padded column stride

@@ -44,7 +44,7 @@ constexpr int kCT = 256;  // threads per workgroup of the complex kernels
 // them there is the traffic of the states (0.5 MB each at 9 x 9, D = 6, complex64, two or three per workgroup
 // against an L2 of 4 MB for 32), hence sites in pairs and the tail in LDS, one pass over the state for each.
 // 9 x 9, D = 6, complex64, 96 samples, against 256 threads, one site per pass and one workgroup per sample:
-// row states 15.8 -> 1.7 ms, O 81.5 -> 6.6, E_loc 59.1 -> 11.0.
+// row states 15.8 -> 1.7 ms, O 81.5 -> 5.4, E_loc 59.1 -> 11.0.
 constexpr int kCxWide = 768;
 
 // complex numbers of the contractions: cxt<double> (complex128) or cxt<float> (complex64); the tVMC
@@ -1138,6 +1138,11 @@ k_cx_logderiv(Dims d, const double* __restrict__ proj, const uint8_t* __restrict
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / CPW, cl = lane - grp * CPW;  // groups beyond Dk^2 (Dk = 3: one lane) hold no columns
   const int gh = grp / Dk, gu = grp - gh * Dk;
+  // with many columns in global memory a wave takes one h instead, and each lane a column's whole share of it:
+  // consecutive columns on consecutive lanes, 27 sums in registers (complex64; complex128 would spill).  With
+  // lane groups seven columns of 8 bytes shared a load's 64 lanes: 9 x 9, D = 6, 96 samples, O 6.6 -> 5.4 ms
+  constexpr bool kByLeg = NT == kCxWide && Dk == 3 && sizeof(RT) == sizeof(float);
+  const int wh = __builtin_amdgcn_readfirstlane(wave % Dk);
   for (int item = blockIdx.x; item < B * L; item += gridDim.x) {
     const int b = item % B, y = item / B;
     cx* Oy = reinterpret_cast<cx*>(O) + ((size_t)b * d.n_sites + (size_t)y * L) * P4;
@@ -1159,40 +1164,73 @@ k_cx_logderiv(Dims d, const double* __restrict__ proj, const uint8_t* __restrict
       const unsigned tail = (unsigned)ipow(Dk, L - x - 1);
       const C* Gx = G + (size_t)x * W;
       // summed in FP64 (each product formed from the stored states, whose precision is the handle's)
-      cx acc[Dk][Dk];
-#pragma unroll
-      for (int q = 0; q < D2; ++q) acc[q / Dk][q % Dk] = cx{0.0, 0.0};
-      if (grp < D2) {
-#pragma unroll 4
-        for (unsigned k = wave * CPW + cl; k < ncol; k += (NT / 64) * CPW) {
-          const unsigned A = k / tail, R = k - A * tail;
-          const size_t base = (size_t)A * D2 * tail + R;
-          cx f[Dk], g[Dk];
-#pragma unroll
-          for (int q = 0; q < Dk; ++q) {
-            f[q] = to_d(F[base + (size_t)(gh * Dk + q) * tail]);
-            g[q] = to_d(Gx[base + (size_t)(gu * Dk + q) * tail]);
-          }
-#pragma unroll
-          for (int q = 0; q < Dk; ++q)
-#pragma unroll
-            for (int hp = 0; hp < Dk; ++hp) acc[q][hp] = cfma(f[q], g[hp], acc[q][hp]);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < D2; ++q) {
-        cx& a = acc[q / Dk][q % Dk];
-        a = cx{group_sum<CPW>(a.re, cl), group_sum<CPW>(a.im, cl)};
-      }
-      if (grp < D2 && cl == 0)
+      if constexpr (kByLeg) {
+        cx acc[Dk][D2];
 #pragma unroll
         for (int q = 0; q < Dk; ++q)
 #pragma unroll
-          for (int hp = 0; hp < Dk; ++hp) part[wave][((gh * Dk + hp) * Dk + q) * Dk + gu] = acc[q][hp];
+          for (int t = 0; t < D2; ++t) acc[q][t] = cx{0.0, 0.0};
+        for (unsigned k = (wave / Dk) * 64 + lane; k < ncol; k += (NT / 64 / Dk) * 64) {
+          const unsigned A = k / tail, R = k - A * tail;
+          const unsigned base = (A * D2 * tail + R) * (unsigned)sizeof(C);
+          C f[Dk], g[D2];
+#pragma unroll
+          for (int q = 0; q < Dk; ++q)
+            f[q] = *reinterpret_cast<const C*>(reinterpret_cast<const char*>(F + (size_t)(wh * Dk + q) * tail) + base);
+#pragma unroll
+          for (int t = 0; t < D2; ++t)
+            g[t] = *reinterpret_cast<const C*>(reinterpret_cast<const char*>(Gx + (size_t)t * tail) + base);
+#pragma unroll
+          for (int t = 0; t < D2; ++t) {
+            const cx gt = to_d(g[t]);
+#pragma unroll
+            for (int q = 0; q < Dk; ++q) acc[q][t] = cfma(to_d(f[q]), gt, acc[q][t]);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < Dk; ++q)
+#pragma unroll
+          for (int t = 0; t < D2; ++t) {
+            const double re = wave_sum_dpp(acc[q][t].re), im = wave_sum_dpp(acc[q][t].im);
+            // t = (u, h') of G's layout -> [h][h'][d][u]
+            if (lane == 0) part[wave][((wh * Dk + t % Dk) * Dk + q) * Dk + t / Dk] = cx{re, im};
+          }
+      } else {
+        cx acc[Dk][Dk];
+#pragma unroll
+        for (int q = 0; q < D2; ++q) acc[q / Dk][q % Dk] = cx{0.0, 0.0};
+        if (grp < D2) {
+#pragma unroll 4
+          for (unsigned k = wave * CPW + cl; k < ncol; k += (NT / 64) * CPW) {
+            const unsigned A = k / tail, R = k - A * tail;
+            const size_t base = (size_t)A * D2 * tail + R;
+            cx f[Dk], g[Dk];
+#pragma unroll
+            for (int q = 0; q < Dk; ++q) {
+              f[q] = to_d(F[base + (size_t)(gh * Dk + q) * tail]);
+              g[q] = to_d(Gx[base + (size_t)(gu * Dk + q) * tail]);
+            }
+#pragma unroll
+            for (int q = 0; q < Dk; ++q)
+#pragma unroll
+              for (int hp = 0; hp < Dk; ++hp) acc[q][hp] = cfma(f[q], g[hp], acc[q][hp]);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < D2; ++q) {
+          cx& a = acc[q / Dk][q % Dk];
+          a = cx{group_sum<CPW>(a.re, cl), group_sum<CPW>(a.im, cl)};
+        }
+        if (grp < D2 && cl == 0)
+#pragma unroll
+          for (int q = 0; q < Dk; ++q)
+#pragma unroll
+            for (int hp = 0; hp < Dk; ++hp) part[wave][((gh * Dk + hp) * Dk + q) * Dk + gu] = acc[q][hp];
+      }
       __syncthreads();
       if (e < P4) {
         cx env{0.0, 0.0};
-        for (int k = 0; k < NT / 64; ++k) env = cadd(env, part[k][e]);
+        for (int k = kByLeg ? l : 0; k < NT / 64; k += kByLeg ? Dk : 1) env = cadd(env, part[k][e]);
         const int dl = x > 0 ? Dk : 1, dr = x < L - 1 ? Dk : 1;
         if (l < dl && r < dr && dd < ddm && u < du) Oy[(size_t)x * P4 + ((l * dr + r) * ddm + dd) * du + u] = env;
       }

@@ -28,6 +28,7 @@
 
 #include "dev_common.h"
 #include "internal.h"
+#include "jacobi_scalar.h"
 
 namespace gipeps {
 
@@ -394,10 +395,11 @@ __device__ __forceinline__ void pair_rotations(double gs0, double gs1, Col& u0, 
   }
 }
 
-// hb: the hand-over buffers (2 ceil(nc/2) columns of MAXN doubles, of MAXN + 8 at the large-bond size) and ring: the rotation ring (4
-// rounds of MAXN/2 (alpha, beta) pairs); both in LDS, as sScl (MAXN scales handed over).  With A and J themselves in LDS they overlay them
-// (hb = A, ring = J: both are dead while the sweeps run); with A and J in global memory (the
-// large-bond kernel) they are separate LDS buffers.  JL0: first lane of the J rows.
+// hb: the hand-over buffers (2 ceil(nc/2) columns of MAXN doubles, of MAXN + 8 at the large-bond size) and
+// ring: the rotation ring (4 rounds of MAXN/2 (alpha, beta) pairs), both in LDS, as sScl (the scales,
+// JacobiScales::room entries).  With A and J themselves in LDS they overlay them (hb = A, ring = J: both are
+// dead while the sweeps run); with A and J in global memory (the large-bond kernel) they are separate LDS
+// buffers.  JL0: first lane of the J rows.
 template <int MAXN, int GW, int NT, int JL0>
 __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J, double* sSig,
                                            int* sPerm, int* sFlag, double* sScal, double2* sScl,
@@ -499,8 +501,10 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
   int* id2 = sPerm + ng;
   double* nrm1 = sSig;  // norms travelling with the handed-over columns
   double* nrm2 = sSig + ng;
-  double2* scl1 = sScl;  // scales (d, 1/d) travelling with them
-  double2* scl2 = sScl + ng;
+  const JacobiScales scales{ng};
+  double2* scl1 = sScl + scales.lower(0);  // scales (d, 1/d) travelling with them
+  double2* scl2 = sScl + scales.upper(0);
+  double2* sclE = sScl + scales.end(0);  // the sweep's final ones
   int rnd = 0;  // round counter (all threads)
 
   // round (2k, 2k+1) with slot 2k in u and slot 2k+1 in v; afterwards the slots are exchanged,
@@ -865,8 +869,8 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
           }
         }
         if (gl == 0) {
-          sScl[NC / 2 * k] = make_double2(cX.d, cY.d);
-          if constexpr (NC == 4) sScl[NC / 2 * k + 1] = make_double2(cZ.d, cV.d);
+          sclE[NC / 2 * k] = make_double2(cX.d, cY.d);
+          if constexpr (NC == 4) sclE[NC / 2 * k + 1] = make_double2(cZ.d, cV.d);
         }
       }
       if (rot_any) sFlag[0] = 1;
@@ -875,7 +879,7 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
       if (jact) {
 #pragma unroll
         for (int q = 0; q < HQ; q += 2) {
-          const double2 f = sScl[jb / 2 + q / 2];
+          const double2 f = sclE[jb / 2 + q / 2];
           Jr[q] *= f.x;
           Jr[q + 1] *= f.y;
           Jr[HQ + q] *= f.x;
@@ -1164,6 +1168,7 @@ __device__ __forceinline__ void row_sweep_body(const Dims& d, const int* __restr
   constexpr int lda = MAXN + 1, ldj = MAXN + 1;  // the Jacobi's padded column stride
   constexpr int SPT = (MAXM * KCH + NT - 1) / NT;
   static_assert(KCH >= 4 && MAXM * KCH <= SBSIZE, "staging chunk fits sB");
+  static_assert(2 * JacobiScales::room(MAXN, jacobi_columns<MAXN, GW>()) <= SBSIZE, "the Jacobi's scales fit sB");
   int chi_next = 1;
   bool converged = true;  // every SVD of the row (same value on every thread)
   for (int i = threadIdx.x; i < m_last; i += NT) sB[i] = sX[i];  // Theta_{L-1}

@@ -241,36 +241,6 @@ __device__ __forceinline__ void householder_qr(double* X, int m, int n, double* 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rotation arithmetic of the Jacobi step.  The Jacobi scales its matrix by a power of two so that
-// ||A||_F^2 is of order one, which keeps every argument below a normal number far from the
-// exponent limits; the square root and reciprocal therefore use the hardware estimates refined by
-// Newton steps, without the rescaling and special-value handling of the library routines.
-// ---------------------------------------------------------------------------------------------
-// t = tan(theta) of the smaller rotation angle annihilating a_i.a_j, from dd = |a_j|^2 - |a_i|^2
-// and g2 = 2 a_i.a_j (g2 != 0): t = sign(dd) g2 / (|dd| + sqrt(dd^2 + g2^2)).  The hardware estimates
-// are good to 2^-24 (measured); one Goldschmidt step for the square root and one Newton step for the reciprocal
-// leave t within a few ulp.  The angle need not be exact to the last bit (the next sweep removes any
-// residue), only cos and sin must be consistent, which rsqrt_1to2 ensures.
-__device__ __forceinline__ double rotation_tangent(double dd, double g2) {
-  const double x = fma(dd, dd, g2 * g2);
-  const double y0 = __builtin_amdgcn_rsq(x);
-  const double g = x * y0;
-  const double root = fma(g, fma(-g, 0.5 * y0, 0.5), g);  // sqrt(x)
-  const double den = fabs(dd) + root;
-  const double y1 = __builtin_amdgcn_rcp(den);
-  const double y = fma(y1, fma(-den, y1, 1.0), y1);
-  return (dd < 0.0 ? -g2 : g2) * y;
-}
-
-// 1 / sqrt(a) for a in [1, 2]: the estimate and one third-order step, y (1 + e/2 + 3 e^2/8) with
-// e = 1 - a y^2, whose error is below e^3
-__device__ __forceinline__ double rsqrt_1to2(double a) {
-  const double y = __builtin_amdgcn_rsq(a);
-  const double e = fma(-a * y, y, 1.0);
-  return fma(y * e, fma(0.375, e, 0.5), y);
-}
-
-// ---------------------------------------------------------------------------------------------
 // One-sided Jacobi (Hestenes) on the nr x nc matrix A (nr >= nc), column j at A + j*ld: rotate
 // column pairs until all are mutually orthogonal, accumulating the rotations in J (nc x nc, column
 // j at J + j*ld, starts as identity), so A_in J = A_out with orthogonal columns.  A pair is left
@@ -315,39 +285,6 @@ __device__ __forceinline__ double group_sum(double v) {
   return v;
 }
 
-// A column's squared norm (carried, not recomputed), its scale and the scale's inverse
-struct Col {
-  double n, d, id;
-};
-// The rotation of the pair (u, v) from u^ . v^ (gs): the factors of the scaled update, u^' = u^ - alpha v^
-// and v^' = v^ + beta u^ (0 when the pair is left alone); norms and scales are advanced.
-struct PairRot {
-  double alpha, beta;
-  bool on;
-};
-__device__ __forceinline__ PairRot pair_rotation(double gs, Col& u, Col& v, double zero2, double tol2, bool& big_any) {
-  constexpr double kQuadratic2 = 1e-12;  // (1e-6)^2
-  const double g = gs * (u.d * v.d);
-  const double gg = g * g, ab = u.n * v.n;
-  const bool pos = fmin(u.n, v.n) > zero2;
-  big_any |= pos && gg > kQuadratic2 * ab;
-  PairRot r{0.0, 0.0, pos && gg > tol2 * ab};
-  if (r.on) {
-    const double t = rotation_tangent(v.n - u.n, g + g);
-    const double a = fma(t, t, 1.0);
-    const double c = rsqrt_1to2(a), ic = a * c;
-    r.alpha = t * (v.d * u.id);
-    r.beta = t * (u.d * v.id);
-    u.n = fma(-t, g, u.n);
-    v.n = fma(t, g, v.n);
-    u.d *= c;
-    v.d *= c;
-    u.id *= ic;
-    v.id *= ic;
-  }
-  return r;
-}
-
 // Columns per group of GW lanes.  Four, for the large bonds: half of the boundary pairs are then a group's own
 // and a quarter of the columns are handed over in a round, not half, where the hand-over is what a round waits
 // for (128 columns of 1 KB, 2.5 k LDS cycles of a round pair with groups of two): 14 x 14, chi 64, 96 samples,
@@ -355,45 +292,6 @@ __device__ __forceinline__ PairRot pair_rotation(double gs, Col& u, Col& v, doub
 // fewer waves run two chains each (a row at 32 columns 1.93 -> 3.5 ms, at 72 6.5 -> 7.3).
 template <int MAXN, int GW>
 constexpr int jacobi_columns() { return MAXN == kMaxNBig && GW == 8 ? 4 : 2; }
-
-// Two pairs at once, without a branch between them, so that their chains (a hundred dependent instructions
-// each) interleave; a pair left alone gets the factors 0 and keeps its norms and scales.
-__device__ __forceinline__ void pair_rotations(double gs0, double gs1, Col& u0, Col& v0, Col& u1, Col& v1, double zero2,
-                                               double tol2, bool& big_any, PairRot& r0, PairRot& r1) {
-  constexpr double kQuadratic2 = 1e-12;
-  const double g0 = gs0 * (u0.d * v0.d), g1 = gs1 * (u1.d * v1.d);
-  const double gg0 = g0 * g0, ab0 = u0.n * v0.n, gg1 = g1 * g1, ab1 = u1.n * v1.n;
-  const bool pos0 = fmin(u0.n, v0.n) > zero2, pos1 = fmin(u1.n, v1.n) > zero2;
-  big_any |= (pos0 && gg0 > kQuadratic2 * ab0) || (pos1 && gg1 > kQuadratic2 * ab1);
-  r0 = PairRot{0.0, 0.0, pos0 && gg0 > tol2 * ab0};
-  r1 = PairRot{0.0, 0.0, pos1 && gg1 > tol2 * ab1};
-  if (r0.on || r1.on) {
-    double t0 = rotation_tangent(v0.n - u0.n, g0 + g0), t1 = rotation_tangent(v1.n - u1.n, g1 + g1);
-    t0 = r0.on ? t0 : 0.0;
-    t1 = r1.on ? t1 : 0.0;
-    const double a0 = fma(t0, t0, 1.0), a1 = fma(t1, t1, 1.0);
-    double c0 = rsqrt_1to2(a0), c1 = rsqrt_1to2(a1);
-    c0 = r0.on ? c0 : 1.0;
-    c1 = r1.on ? c1 : 1.0;
-    const double ic0 = a0 * c0, ic1 = a1 * c1;
-    r0.alpha = t0 * (v0.d * u0.id);
-    r0.beta = t0 * (u0.d * v0.id);
-    r1.alpha = t1 * (v1.d * u1.id);
-    r1.beta = t1 * (u1.d * v1.id);
-    u0.n = fma(-t0, g0, u0.n);
-    v0.n = fma(t0, g0, v0.n);
-    u1.n = fma(-t1, g1, u1.n);
-    v1.n = fma(t1, g1, v1.n);
-    u0.d *= c0;
-    v0.d *= c0;
-    u1.d *= c1;
-    v1.d *= c1;
-    u0.id *= ic0;
-    v0.id *= ic0;
-    u1.id *= ic1;
-    v1.id *= ic1;
-  }
-}
 
 // hb: the hand-over buffers (2 ceil(nc/2) columns of MAXN doubles, of MAXN + 8 at the large-bond size) and
 // ring: the rotation ring (4 rounds of MAXN/2 (alpha, beta) pairs), both in LDS, as sScl (the scales,

@@ -9,6 +9,7 @@ Rotation arithmetic, with the hardware's estimates replaced by ones that are off
 2^-53 below).  t = s / (|dd| + sqrt(dd^2 + g2^2)): the sum of squares is within 2 u, its root within 2 u (half of
 that and its own rounding), the denominator within 3 u, the quotient within 4 u; what the refinements leave out is of
 the order of 2^-68.
+1 / sqrt(a): rounded once, so within 2^-54, which is 2^-53 / sqrt(2) of the smallest value, 1 / sqrt(2).
 """
 import os
 import subprocess
@@ -30,7 +31,12 @@ static double off(long double v) {  // an estimate of v, off by up to 2^-24 of i
   b ^= b >> 33; b *= 0xff51afd7ed558ccdULL; b ^= b >> 33; b *= 0xc4ceb9fe1a85ec53ULL; b ^= b >> 33;
   return (double)(v * (1 + ((double)(b >> 11) / 4503599627370496.0 - 1) * std::ldexp(1.0L, -24)));
 }
-static double __builtin_amdgcn_rsq(double x) { return off(1 / std::sqrt((long double)x)); }
+static double __builtin_amdgcn_rsq(double x) {
+  const long double v = 1 / std::sqrt((long double)x);
+  if (x == 1.0) return 1.0;                                            // as the hardware has it
+  if (v < 1 && v > 1 - std::ldexp(1.0L, -28)) return 1 - std::ldexp(1.0, -53);
+  return off(v);
+}
 static double __builtin_amdgcn_rcp(double x) { return off(1 / (long double)x); }
 #include "jacobi_scalar.h"
 """
@@ -91,3 +97,20 @@ int main() {
 }
 """ % seed)[0])
     assert worst <= 4.01, "%.2f units of 2^-53" % worst
+
+
+def test_inverse_root_is_rounded_once(tmp_path):
+    worst = float(host_program(tmp_path, HEAD + """
+int main() {
+  std::mt19937_64 r(3);
+  std::uniform_real_distribution<double> u;
+  long double worst = 0;
+  for (int i = 0; i < 400000; ++i) {
+    const double t = i & 1 ? u(r) : std::pow(10, -3 - 5 * u(r)), a = fma(t, t, 1.0);  // any angle; a small one
+    const long double c = 1 / std::sqrt((long double)a);
+    worst = std::max(worst, std::fabs((gipeps::rsqrt_1to2(a) - c) / c));
+  }
+  printf("%.6Lf", worst * std::ldexp(1.0L, 53));
+}
+""")[0])
+    assert worst <= 0.5 ** 0.5 * 1.0001, "%.3f units of 2^-53" % worst

@@ -143,7 +143,7 @@ CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what, bool split) {
   w.slots = split ? cx_split_slots(d, B) : B;
   w.gscr = take(cxs * w.slots * L * W);
   w.wscr = take(cx_work_global(d) ? cxs * w.slots * 2 * W : 0);
-  w.epart = take(w.slots > B ? cxb * Bz * (L - 1) : 0);
+  w.epart = take(w.slots > B ? cxb * Bz * cx_eloc_terms(d.L, d.N) : 0);
   // the slots beyond the batch take the same bytes for either precision of the states
   off += (size_t)(w.slots - B) * (cxb - cxs) * (cx_work_global(d) ? L + 2 : L) * W;
   w.base_end = off = align256(off);

@@ -278,6 +278,9 @@ size_t cx_work(const Dims& d);         // Dk^(L+1): entries of one working state
 inline size_t cx_elem_bytes(const Dims& d) { return d.cx32 ? 2 * sizeof(float) : 2 * sizeof(double); }
 // slots of backward and working states that E_loc and the log-derivatives of B samples run in (>= B)
 int cx_split_slots(const Dims& d, int B);
+// what the split E_loc keeps per sample (complex128): the ratio of each plaquette and power in the order of their
+// sum, a flag per pair of rows, the electric part
+__host__ __device__ inline int cx_eloc_terms(int L, int N) { return (L - 1) * (L - 1) * (N - 1) + L; }
 bool cx_work_global(const Dims& d);    // working states above kCxMaxWork live in a global slot (wscr)
 hipError_t launch_cx_project(const Dims& d, const DeviceTables& t, const double* theta, const uint8_t* links,
                              int B, double* proj, int32_t* block_id, uint8_t* valid, hipStream_t s);
@@ -321,7 +324,7 @@ struct CxWs {
   int slots;       // slots of gscr and wscr: B, or cx_split_slots when the workspace holds them
   size_t gscr;     // double [slots][L][Dk^(L+1)][2]  backward states of one row
   size_t wscr;     // double [slots][2][Dk^(L+1)][2]  working states (only above kCxMaxWork entries)
-  size_t epart;    // double [B][L-1][2]            E_loc per pair of rows (only if slots > B)
+  size_t epart;    // double [B][cx_eloc_terms][2]  ratios of E_loc (only if slots > B)
   size_t w;        // double [B]                     sample weights
   size_t ov;       // double [B][2]                  O_b . v
   size_t sc;       // double [kCxScalars]            <E>, CG scalars

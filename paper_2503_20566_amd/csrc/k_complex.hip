@@ -800,6 +800,9 @@ __device__ cx strip_meet(const cxt<RT>* F, cxt<RT>* w0, cxt<RT>* w1, const cxt<R
   return dot_cx<1>(a, G + (size_t)(px + 1) * W, W, red);
 }
 
+// off + ct r, of the local energy's sum over plaquettes and powers
+__device__ __forceinline__ cx add_ratio(cx off, double ct, cx r) { return cx{fma(ct, r.re, off.re), fma(ct, r.im, off.im)}; }
+
 // E_loc (complex) of every valid sample; NaN where a strip's denominator vanishes.
 //
 // The ratio of plaquette p = (px, py) is <V_py R'_py R'_py+1, Top_py+2> over the same with the
@@ -816,7 +819,7 @@ k_cx_eloc(Dims d, const int64_t* __restrict__ site_offset, const int8_t* __restr
           const double* __restrict__ plaq, const double* __restrict__ elec, const double* __restrict__ theta,
           const uint8_t* __restrict__ links, const double* __restrict__ proj, const uint8_t* __restrict__ valid,
           const double* __restrict__ states, double* __restrict__ e_loc, double* __restrict__ gscr,
-          double* __restrict__ wscr, int B, int groups) {
+          double* __restrict__ wscr, int B, int groups, double* __restrict__ terms) {
   extern __shared__ __align__(16) double smem[];
   __shared__ double red[NT / 64];
   const CxShape c = cx_shape(d);
@@ -833,14 +836,14 @@ k_cx_eloc(Dims d, const int64_t* __restrict__ site_offset, const int8_t* __restr
   // item (g, b): the pairs [g per, (g + 1) per) of sample b
   for (int item = blockIdx.x; item < B * groups; item += gridDim.x) {
   const int b = item % B, grp = item / B;
-  double* out = e_loc + 2 * ((size_t)b * groups + grp);
   if (!valid[b]) {
-    if (threadIdx.x == 0) {
-      out[0] = NAN;
-      out[1] = NAN;
+    if (threadIdx.x == 0 && groups == 1) {
+      e_loc[2 * b] = NAN;
+      e_loc[2 * b + 1] = NAN;
     }
     continue;
   }
+  cx* tb = reinterpret_cast<cx*>(terms) + (size_t)b * cx_eloc_terms(L, N);  // split: the sample's ratios
   const cx* pb = reinterpret_cast<const cx*>(proj) + (size_t)b * d.n_sites * P4;
   const C* st = reinterpret_cast<const C*>(states) + (size_t)b * 2 * (L + 1) * S;
   const uint8_t* lk = links + (size_t)b * d.planes * L * L;
@@ -921,12 +924,17 @@ k_cx_eloc(Dims d, const int64_t* __restrict__ site_offset, const int8_t* __restr
         const cx num = dot_cx<NT == kCxWide ? 8 : 1>(NT == kCxWide && whole ? w1 : w0, whole ? top : G + (size_t)(px + 1) * W, whole ? S : W, red);
         if (t == 0) {
           den = num;
-          if (den.re == 0.0 && den.im == 0.0) finite = false;
+          const bool zero = den.re == 0.0 && den.im == 0.0;
+          if (zero) finite = false;
+          if (groups > 1 && threadIdx.x == 0) tb[cx_eloc_terms(L, N) - L + py] = cx{zero ? 1.0 : 0.0, 0.0};
           continue;
         }
         swap_blocks();
         const cx r = cdiv(num, den);
-        off = cadd(off, cx{ct * r.re, ct * r.im});
+        if (groups == 1)
+          off = add_ratio(off, ct, r);
+        else if (threadIdx.x == 0)
+          tb[(py * (L - 1) + px) * (N - 1) + t - 1] = r;
       }
       // F: absorb the sample's site px of row py
       if (px + 1 < L - 1) {
@@ -942,22 +950,40 @@ k_cx_eloc(Dims d, const int64_t* __restrict__ site_offset, const int8_t* __restr
     }
   }
   if (threadIdx.x == 0) {
-    out[0] = finite ? el + off.re : NAN;
-    out[1] = finite ? off.im : NAN;
+    if (groups == 1) {
+      e_loc[2 * b] = finite ? el + off.re : NAN;
+      e_loc[2 * b + 1] = finite ? off.im : NAN;
+    } else if (grp == 0) {
+      tb[cx_eloc_terms(L, N) - 1] = cx{el, 0.0};
+    }
   }
   __syncthreads();  // the next item's tensors
   }
 }
 
-// E_loc of a sample from its groups of row pairs, in their order
-__global__ void __launch_bounds__(kCT)
-k_cx_eloc_sum(int B, int groups, const double* __restrict__ part, double* __restrict__ e_loc) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  cx e{0.0, 0.0};
-  for (int g = 0; g < groups; ++g) e = cadd(e, cx{part[2 * ((size_t)b * groups + g)], part[2 * ((size_t)b * groups + g) + 1]});
-  e_loc[2 * b] = e.re;
-  e_loc[2 * b + 1] = e.im;
+// E_loc of a sample whose row pairs were split over workgroups, from its ratios, added as the unsplit loop adds
+// them: the same bits for every batch size and workspace.  One wave per sample, which loads 64 ratios at once.
+__global__ void __launch_bounds__(64)
+k_cx_eloc_sum(int L, int N, const double* __restrict__ plaq, const uint8_t* __restrict__ valid,
+              const double* __restrict__ terms, double* __restrict__ e_loc) {
+  const int b = blockIdx.x, lane = threadIdx.x, all = cx_eloc_terms(L, N), nr = all - L;
+  const cx* tb = reinterpret_cast<const cx*>(terms) + (size_t)b * all;
+  cx off{0.0, 0.0};
+  bool finite = valid[b] != 0;
+  if (finite) {  // the same on every lane
+    for (int q0 = 0; q0 < nr; q0 += 64) {
+      const int q = q0 + lane;
+      const double ct = q < nr ? plaq[1 + q % (N - 1)] : 0.0;
+      const cx r = ct != 0.0 ? tb[q] : cx{0.0, 0.0};  // (ratios of no coupling are not formed)
+      for (int i = 0; i < min(64, nr - q0); ++i)
+        off = add_ratio(off, __shfl(ct, i, 64), cx{__shfl(r.re, i, 64), __shfl(r.im, i, 64)});
+    }
+    for (int py = 0; py < L - 1; ++py) finite = finite && tb[nr + py].re == 0.0;
+  }
+  if (lane == 0) {
+    e_loc[2 * b] = finite ? tb[all - 1].re + off.re : NAN;
+    e_loc[2 * b + 1] = finite ? off.im : NAN;
+  }
 }
 
 // One Metropolis sweep of complex chains with strip ratios (SM S-2 configuration sampling; the
@@ -1689,11 +1715,10 @@ hipError_t launch_cx_eloc_t(const Dims& d, const DeviceTables& t, const double* 
   const int groups = slots > B ? d.L - 1 : 1;
   const int grid = (int)std::min<long>(slots, (long)B * groups);
   hipLaunchKernelGGL((k_cx_eloc<Dk, RT, NT>), dim3(grid), dim3(NT), cx_lds_bytes(d, 1), s, d, t.site_offset, t.Q,
-                     t.plaq, t.elec, theta, links, proj, valid, states, groups > 1 ? epart : e_loc, gscr,
-                     cx_work_global(d) ? wscr : nullptr, B, groups);
+                     t.plaq, t.elec, theta, links, proj, valid, states, e_loc, gscr, cx_work_global(d) ? wscr : nullptr, B,
+                     groups, epart);
   if (hipError_t e = hipGetLastError()) return e;
-  if (groups > 1)
-    hipLaunchKernelGGL(k_cx_eloc_sum, dim3((B + kCT - 1) / kCT), dim3(kCT), 0, s, B, groups, epart, e_loc);
+  if (groups > 1) hipLaunchKernelGGL(k_cx_eloc_sum, dim3(B), dim3(64), 0, s, d.L, d.N, t.plaq, valid, epart, e_loc);
   return hipGetLastError();
 }
 

@@ -1,0 +1,52 @@
+"""A sample's complex ln|Psi|, O and E_loc have the same bits in every batch and workspace: in a small batch whose row
+pairs are split over the chip, in the same batch with one slot of working states per sample (no split), and in a batch
+that fills the chip.  With states in LDS and in global memory, a power without coupling (Z4), an invalid sample and
+samples whose amplitude is exactly zero (a block of zeros), which give NaN either way.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle.energy import config_tables
+from oracle.lattice import links_from_powers
+from paper_2503_20566_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("c64", [False, True])
+@pytest.mark.parametrize("L,N,Dk,many", [(3, 2, 1, 800), (4, 4, 2, 800), (6, 2, 3, 800), (7, 2, 3, 260)])
+def test_bits_do_not_depend_on_the_batch(lib, L, N, Dk, many, c64):
+    c, e = config_tables(N, 1.0, 0.4)
+    P = lib.Peps(L, N, Dk, 4, c, e, dtype=lib.PEPS_C64_EXACT if c64 else lib.PEPS_C128_EXACT)
+    rng = np.random.Generator(np.random.PCG64(L * 10 + Dk))
+    theta = 1 + 0.3 * (rng.standard_normal(P.n_params) + 1j * rng.standard_normal(P.n_params))
+    v = N // 2
+    theta[P.site_offset[0] + v * Dk ** 2: P.site_offset[0] + (v + 1) * Dk ** 2] = 0   # site (0, 0), links v and -v
+    th = torch.from_numpy(theta).cuda()
+    few = 5
+    powers = synth.plaquette_powers(many, L, N, seed=5)
+    links = np.stack([links_from_powers(powers[b], N) for b in range(many)])
+    links[3, 0, 1, 1] = (links[3, 0, 1, 1] + 1) % N                          # not a state of the Gauss law
+
+    def values(B, nbytes=None):
+        lk = torch.from_numpy(links[:B]).cuda()
+        proj, _, valid = P.cx_project(th, lk)
+        assert not valid[3] and int(valid.sum()) == B - 1
+        ws = torch.zeros(nbytes or P.workspace_bytes(B, lib.PEPS_WS_AMPLITUDE), dtype=torch.uint8, device="cuda")
+        la, ph = P.cx_amplitude(proj, valid, ws)
+        O = P.cx_logderiv(proj, valid, ws)
+        E = P.cx_local_energy(th, lk, proj, valid, ws)
+        return [np.ascontiguousarray(t[:few].cpu().numpy()).view(np.float64) for t in (la, ph, O, E)]
+
+    S, W, cb = Dk ** L, Dk ** (L + 1), 8 if c64 else 16
+    up = lambda n: (n + 255) // 256 * 256
+    small = up(cb * few * 2 * (L + 1) * S) + up(8 * few * 2 * (L + 1)) + up(cb * few * L * W)
+    small += up(cb * few * 2 * W) if W > 2187 else 0
+    split, plain, large = values(few), values(few, small), values(many)
+    zero = np.array([links[b, 0, 0, 0] == v for b in range(few)])
+    E = split[3].reshape(few, 2)
+    assert (np.isnan(E).all(1) == (zero | (np.arange(few) == 3))).all() and zero.any() and not zero.all()
+    for name, a, b, w in zip(("ln|Psi|", "phase", "O", "E_loc"), split, plain, large):
+        assert np.array_equal(a.view(np.uint64), b.view(np.uint64)), name + ": workspace"
+        assert np.array_equal(a.view(np.uint64), w.view(np.uint64)), name + ": batch"

@@ -437,9 +437,12 @@ int peps_autotune(peps_handle* h, const double* proj, const uint8_t* valid, int3
  * these calls return PEPS_ERR_ARG for real handles).  Supported: pure gauge (matter = 0, background charges allowed),
  * uniform Dk <= 3, Dk^(L+1) <= 177147 (L <= 16 at Dk = 2, L <= 10 at Dk = 3), keep_tape = 0; chi
  * is not used.  Up to Dk^(L+1) = 2187 a sample's two working states stay in LDS; above, they take a
- * slot of the workspace (2 Dk^(L+1) complex per sample).  Batches smaller than the workgroups that
- * the chip holds get further slots, over which E_loc and O spread a sample's rows; a workspace with
- * one slot per sample serves as well.  Complex numbers are interleaved (re, im) float64 pairs: theta is float64
+ * slot of the workspace (2 Dk^(L+1) complex per sample).  A batch smaller than the workgroups that
+ * the handle's device holds at once (one per compute unit with the states in the workspace, three
+ * with them in LDS) gets further slots of (L + 2) Dk^(L+1) (L Dk^(L+1)) complex, up to L per sample,
+ * over which E_loc and O spread a sample's rows: at 10 x 10, Dk = 3, complex64 a slot is 17 MB, and
+ * 26 samples take 4.6 GB instead of 0.7.  A workspace with one slot per sample, as reported for a
+ * handle without a device, serves as well; the results have the same bits either way.  Complex numbers are interleaved (re, im) float64 pairs: theta is float64
  * [n_params][2] in the parameter layout above.  PEPS_C64_EXACT runs the contractions (row states,
  * site absorptions, environments) in complex64, with the row states' power-of-two exponents, the
  * overlaps and ratios, ln|Psi|, and every input and output in float64 as above; the workspace's

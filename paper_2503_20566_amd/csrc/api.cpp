@@ -110,6 +110,7 @@ int ensure_device(peps_handle* h) {
     free_tables(h);
     return PEPS_ERR_HIP;
   }
+  if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) h->cus = 0;
   h->device = dev;
   return PEPS_OK;
 }
@@ -140,13 +141,11 @@ CxWs cx_ws_layout(const peps_handle* h, int B, uint32_t what, bool split) {
   };
   w.states = take(cxs * Bz * 2 * (L + 1) * S);
   w.expo = take(sizeof(double) * Bz * 2 * (L + 1));
-  w.slots = split ? cx_split_slots(d, B) : B;
+  w.slots = split ? cx_split_slots(d, h->cus, B) : B;
   w.gscr = take(cxs * w.slots * L * W);
   w.wscr = take(cx_work_global(d) ? cxs * w.slots * 2 * W : 0);
   w.epart = take(w.slots > B ? cxb * Bz * cx_eloc_terms(d.L, d.N) : 0);
-  // the slots beyond the batch take the same bytes for either precision of the states
-  off += (size_t)(w.slots - B) * (cxb - cxs) * (cx_work_global(d) ? L + 2 : L) * W;
-  w.base_end = off = align256(off);
+  w.base_end = off;
   if (what & PEPS_WS_SAMPLE) {
     w.lprop = take((size_t)d.planes * L * L * Bz);
     w.laprop = take(sizeof(double) * Bz);

@@ -67,6 +67,7 @@ struct peps_handle {
   int ckpt_every;
   bool keep_tape;  // amplitude stores every row's factorisations; logderiv reverses them
   int device;
+  int cus = 0;  // compute units of the device, 0 before the handle has one
   double plaq_coef[8];
   double elec[8];
   double hop, mass;  // eq. matter: hopping coupling J and chemical potential m (matter only)
@@ -276,8 +277,9 @@ size_t cx_lds_bytes(const Dims& d, int which);  // 0: states / logderiv kernels,
 size_t cx_work(const Dims& d);         // Dk^(L+1): entries of one working state
 // bytes of one complex entry of the contractions' states: 8 (complex64) or 16 (complex128)
 inline size_t cx_elem_bytes(const Dims& d) { return d.cx32 ? 2 * sizeof(float) : 2 * sizeof(double); }
-// slots of backward and working states that E_loc and the log-derivatives of B samples run in (>= B)
-int cx_split_slots(const Dims& d, int B);
+// slots of backward and working states that E_loc and the log-derivatives of B samples run in (>= B) on a device
+// of cus compute units
+int cx_split_slots(const Dims& d, int cus, int B);
 // what the split E_loc keeps per sample (complex128): the ratio of each plaquette and power in the order of their
 // sum, a flag per pair of rows, the electric part
 __host__ __device__ inline int cx_eloc_terms(int L, int N) { return (L - 1) * (L - 1) * (N - 1) + L; }

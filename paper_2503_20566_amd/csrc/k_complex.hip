@@ -1702,8 +1702,8 @@ hipError_t launch_cx_states(const Dims& d, const double* proj, const uint8_t* va
 // global memory, three with it in LDS) are run as B (L - 1) (B L) items over that many workgroups, each with a
 // slot of its own.  9 x 9, D = 6, complex64, 96 samples, one workgroup per sample and split: E_loc 21.9 -> 11.4
 // ms, O 11.5 -> 6.6; 10 x 10, D = 4, complex128, 64 samples, before and after: E_loc 2.2 -> 0.43, O 1.2 -> 0.14.
-int cx_split_slots(const Dims& d, int B) {
-  const long resident = cx_work_global(d) ? 256 : 768;
+int cx_split_slots(const Dims& d, int cus, int B) {
+  const long resident = (cx_work_global(d) ? 1L : 3L) * cus;
   return (int)std::max<long>(B, std::min<long>((long)B * d.L, resident));
 }
 

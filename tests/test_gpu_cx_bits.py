@@ -50,3 +50,15 @@ def test_bits_do_not_depend_on_the_batch(lib, L, N, Dk, many, c64):
     for name, a, b, w in zip(("ln|Psi|", "phase", "O", "E_loc"), split, plain, large):
         assert np.array_equal(a.view(np.uint64), b.view(np.uint64)), name + ": workspace"
         assert np.array_equal(a.view(np.uint64), w.view(np.uint64)), name + ": batch"
+
+
+@pytest.mark.parametrize("L,Dk,B", [(10, 3, 4), (6, 3, 2), (9, 3, 96), (11, 2, 300)])
+def test_slots_take_the_bytes_of_their_precision(lib, L, Dk, B):
+    # row states, and per slot L backward and (above 2187 entries) two working states: 8 bytes apart per entry
+    c, e = config_tables(2, 1.0, 0.4)
+    n = [lib.Peps(L, 2, Dk, 4, c, e, dtype=t).workspace_bytes(B, lib.PEPS_WS_AMPLITUDE)
+         for t in (lib.PEPS_C64_EXACT, lib.PEPS_C128_EXACT)]
+    S, W = Dk ** L, Dk ** (L + 1)
+    per_cu, states = (1, L + 2) if W > 2187 else (3, L)
+    slots = max(B, min(B * L, per_cu * torch.cuda.get_device_properties(0).multi_processor_count))
+    assert abs(n[1] - n[0] - 8 * (B * 2 * (L + 1) * S + slots * states * W)) <= 8 * 256

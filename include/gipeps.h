@@ -85,7 +85,7 @@
  *     Fused bonds from 73 to 128 (Dk = 2, chi <= 64: the Z4 32 x 32, D = 8, chi = 64 study; SM
  *     S-4) run on large-bond kernels whose working matrices live in the workspace rather than in
  *     LDS: every real-tensor entry point except peps_amplitude_noalloc, which refuses such a
- *     handle (their row kernel always runs four Jacobi lanes per column pair, whatever
+ *     handle (their row kernel always runs eight Jacobi lanes per column group, whatever
  *     peps_tuning says); such a problem with keep_tape or var_sweeps is refused by peps_create.
  *     Other shapes return PEPS_ERR_UNSUPPORTED.
  */
@@ -418,12 +418,13 @@ int peps_get_tuning(const peps_handle* h, peps_tuning* t);
  * workspace holds (call peps_amplitude again before peps_local_energy / peps_logderiv). */
 int peps_set_tuning(peps_handle* h, const peps_tuning* t);
 /* Autotuner: times, on the caller's batch (proj, valid of peps_project, B > 0), one down sweep and
- * one up sweep for each candidate -- jacobi_lanes in {8, 4} x precond_min in {16, 32} (x
- * small_waves in {2, 4} when the chi * Dk <= 32 kernels run), each with every down mode and every
- * up mode -- and keeps, over those combinations, the fastest down mode plus the fastest up mode
- * with the smallest sum; that tuning is set on the handle and returned in *best.  results (HOST,
- * capacity entries, or NULL with capacity 0) receives the timings in the order run, *count (HOST,
- * or NULL) their number (20, or 40 with the waves).  ws: sized for PEPS_WS_AMPLITUDE |
+ * one up sweep for each candidate -- jacobi_lanes in {8, 4} (8 alone for fused bonds above 72) x
+ * precond_min in {16, 32}, each with every down mode and every up mode -- and keeps, over those
+ * combinations, the fastest down mode plus the fastest up mode with the smallest sum; that tuning,
+ * with the handle's small_waves, is set on the handle and returned in *best.  results (HOST,
+ * capacity entries, or NULL with capacity 0) receives the timings, *count (HOST, or NULL) their
+ * number: 20, or 10 above 72; 40 where chi * Dk <= 32, each time reported for both values of
+ * small_waves, which chooses no kernel.  ws: sized for PEPS_WS_AMPLITUDE |
  * PEPS_WS_ENERGY; its contents are overwritten and the workspace state is invalidated as by
  * peps_set_tuning.  Synchronises the stream after every candidate; allocates two HIP events. */
 int peps_autotune(peps_handle* h, const double* proj, const uint8_t* valid, int32_t B, void* ws,

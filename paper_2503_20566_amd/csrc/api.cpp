@@ -1335,57 +1335,50 @@ int peps_autotune(peps_handle* h, const double* proj, const uint8_t* valid, int3
   double dummy = 0.0;
   if (e == hipSuccess) e = timed_sweep(false, &dummy);
   if (e == hipSuccess) e = timed_sweep(true, &dummy);
-  // candidates: lanes {8, 4} x threshold {16, 32} (x waves per SIMD {2, 4} where the chi*Dk <= 32
-  // kernels run); per combination the fastest down and up modes.  The large-bond kernel always runs
-  // four lanes per column pair: there only the thresholds and modes are tried.
+  // candidates: lanes {8, 4} x threshold {16, 32}; per combination the fastest down and up modes.  The
+  // large-bond kernels always run eight lanes: there only the thresholds and modes are tried.  The
+  // small_waves of peps_tuning chooses no kernel any more: where it did (fused bonds up to 32) a candidate is
+  // timed once and its time reported for both values.
   const int lanes[2] = {8, 4}, thrs[2] = {16, 32}, waves[2] = {2, 4};
   const int nwaves = (d.Dk == 1 || d.maxN <= 32) ? 2 : 1;
-  const int a0 = d.maxN > kMaxN ? 1 : 0;
+  const int nlanes = d.maxN > kMaxN ? 1 : 2;
   const int dmodes[2] = {PEPS_PRECOND_SORTED_QR, PEPS_PRECOND_NONE};
   const int umodes[3] = {PEPS_PRECOND_QR_T, PEPS_PRECOND_SORTED_QR, PEPS_PRECOND_NONE};
   int n = 0;
   double best_ms = 0.0;
   bool have_best = false;
   peps_tuning bt = saved;
-  auto record = [&](int mode, int upward, double ms) {
+  auto record = [&](int waves_value, int mode, int upward, double ms) {
     if (n < capacity)
-      results[n] = peps_tune_result{d.jacobi_lanes, mode, d.precond_min, d.small_waves, upward, ms};
+      results[n] = peps_tune_result{d.jacobi_lanes, mode, d.precond_min, waves_value, upward, ms};
     ++n;
   };
-  for (int a = a0; a < 2 && e == hipSuccess; ++a)
-    for (int b = 0; b < 2 && e == hipSuccess; ++b)
-      for (int c = 0; c < nwaves && e == hipSuccess; ++c) {
-        d.jacobi_lanes = lanes[a];
-        d.precond_min = thrs[b];
-        d.small_waves = waves[c];
-        double bd = 0.0, bu = 0.0;
-        int md = dmodes[0], mu = umodes[0];
-        for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-          d.down_precond = dmodes[i];
-          double ms = 0.0;
-          e = timed_sweep(false, &ms);
-          record(dmodes[i], 0, ms);
-          if (i == 0 || ms < bd) {
-            bd = ms;
-            md = dmodes[i];
-          }
-        }
-        for (int i = 0; i < 3 && e == hipSuccess; ++i) {
-          d.up_precond = umodes[i];
-          double ms = 0.0;
-          e = timed_sweep(true, &ms);
-          record(umodes[i], 1, ms);
-          if (i == 0 || ms < bu) {
-            bu = ms;
-            mu = umodes[i];
-          }
-        }
-        if (e == hipSuccess && (!have_best || bd + bu < best_ms)) {
-          have_best = true;
-          best_ms = bd + bu;
-          bt = peps_tuning{lanes[a], md, mu, thrs[b], waves[c]};
-        }
+  for (int a = 0; a < nlanes && e == hipSuccess; ++a)
+    for (int b = 0; b < 2 && e == hipSuccess; ++b) {
+      d.jacobi_lanes = lanes[a];
+      d.precond_min = thrs[b];
+      double down_ms[2] = {0.0, 0.0}, up_ms[3] = {0.0, 0.0, 0.0};
+      for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+        d.down_precond = dmodes[i];
+        e = timed_sweep(false, &down_ms[i]);
       }
+      for (int i = 0; i < 3 && e == hipSuccess; ++i) {
+        d.up_precond = umodes[i];
+        e = timed_sweep(true, &up_ms[i]);
+      }
+      if (e != hipSuccess) break;
+      for (int c = 0; c < nwaves; ++c) {
+        for (int i = 0; i < 2; ++i) record(waves[c], dmodes[i], 0, down_ms[i]);
+        for (int i = 0; i < 3; ++i) record(waves[c], umodes[i], 1, up_ms[i]);
+      }
+      const int md = (int)(std::min_element(down_ms, down_ms + 2) - down_ms);
+      const int mu = (int)(std::min_element(up_ms, up_ms + 3) - up_ms);
+      if (!have_best || down_ms[md] + up_ms[mu] < best_ms) {
+        have_best = true;
+        best_ms = down_ms[md] + up_ms[mu];
+        bt = peps_tuning{lanes[a], dmodes[md], umodes[mu], thrs[b], saved.small_waves};
+      }
+    }
   for (hipEvent_t x : ev)
     if (x) (void)hipEventDestroy(x);
   apply_tuning(h, e == hipSuccess ? bt : saved);

@@ -54,6 +54,11 @@ struct alignas(2 * sizeof(RT)) cxt {  // aligned: one LDS access per entry
   RT re, im;
 };
 using cx = cxt<double>;
+// ... of a caller's array (proj, O), which is aligned for its float64 parts only
+struct cxc {
+  double re, im;
+  __device__ __forceinline__ operator cx() const { return cx{re, im}; }
+};
 template <typename RT>
 __device__ __forceinline__ cxt<RT> cadd(cxt<RT> a, cxt<RT> b) { return cxt<RT>{a.re + b.re, a.im + b.im}; }
 template <typename RT>
@@ -143,7 +148,7 @@ __device__ bool gather_padded(const double* theta, const int64_t* site_offset, c
 // Compact projected block (first Dk^#present entries, row-major over the present legs) of site
 // (x, y) into the padded [l][r][d][u] layout.
 template <typename RT>
-__device__ void load_padded(const cx* comp, int L, int Dk, int x, int y, cxt<RT>* dst) {
+__device__ void load_padded(const cxc* comp, int L, int Dk, int x, int y, cxt<RT>* dst) {
   const int dl = x > 0 ? Dk : 1, dr = x < L - 1 ? Dk : 1, dd = y > 0 ? Dk : 1, du = y < L - 1 ? Dk : 1;
   const int P4 = Dk * Dk * Dk * Dk;
   for (int i = threadIdx.x; i < P4; i += blockDim.x) {
@@ -706,7 +711,7 @@ k_cx_states(Dims d, const double* __restrict__ proj, const uint8_t* __restrict__
   using C = cxt<RT>;
   C* w0 = work_state<RT>(smem, wscr, b, W, NT == kCxWide) + (NT == kCxWide ? (size_t)blockIdx.y * W : 0);  // of two
   C* T = row_tensors<RT>(smem, W, NT == kCxWide);  // one row, L x P4
-  const cx* pb = reinterpret_cast<const cx*>(proj) + (size_t)b * d.n_sites * P4;
+  const cxc* pb = reinterpret_cast<const cxc*>(proj) + (size_t)b * d.n_sites * P4;
   C* st = reinterpret_cast<C*>(states) + (size_t)b * 2 * (L + 1) * S;
   double* ex = expo + (size_t)b * 2 * (L + 1);
   // 0: from below (V), 1: from above (Top); both here, or one in each workgroup of the pair
@@ -844,7 +849,7 @@ k_cx_eloc(Dims d, const int64_t* __restrict__ site_offset, const int8_t* __restr
     continue;
   }
   cx* tb = reinterpret_cast<cx*>(terms) + (size_t)b * cx_eloc_terms(L, N);  // split: the sample's ratios
-  const cx* pb = reinterpret_cast<const cx*>(proj) + (size_t)b * d.n_sites * P4;
+  const cxc* pb = reinterpret_cast<const cxc*>(proj) + (size_t)b * d.n_sites * P4;
   const C* st = reinterpret_cast<const C*>(states) + (size_t)b * 2 * (L + 1) * S;
   const uint8_t* lk = links + (size_t)b * d.planes * L * L;
   // electric part (in group 0)
@@ -1171,12 +1176,12 @@ k_cx_logderiv(Dims d, const double* __restrict__ proj, const uint8_t* __restrict
   const int wh = __builtin_amdgcn_readfirstlane(wave % Dk);
   for (int item = blockIdx.x; item < B * L; item += gridDim.x) {
     const int b = item % B, y = item / B;
-    cx* Oy = reinterpret_cast<cx*>(O) + ((size_t)b * d.n_sites + (size_t)y * L) * P4;
+    cxc* Oy = reinterpret_cast<cxc*>(O) + ((size_t)b * d.n_sites + (size_t)y * L) * P4;
     if (!valid[b]) {
-      for (int i = threadIdx.x; i < L * P4; i += blockDim.x) Oy[i] = cx{0.0, 0.0};
+      for (int i = threadIdx.x; i < L * P4; i += blockDim.x) Oy[i] = cxc{0.0, 0.0};
       continue;
     }
-    const cx* pb = reinterpret_cast<const cx*>(proj) + (size_t)b * d.n_sites * P4;
+    const cxc* pb = reinterpret_cast<const cxc*>(proj) + (size_t)b * d.n_sites * P4;
     const C* st = reinterpret_cast<const C*>(states) + (size_t)b * 2 * (L + 1) * S;
     const C* top = st + (size_t)(L + 1 + y + 1) * S;  // Top_{y+1}
     for (int x = 0; x < L; ++x) load_padded(pb + (size_t)(y * L + x) * P4, L, Dk, x, y, T + (size_t)x * P4);
@@ -1258,7 +1263,7 @@ k_cx_logderiv(Dims d, const double* __restrict__ proj, const uint8_t* __restrict
         cx env{0.0, 0.0};
         for (int k = kByLeg ? l : 0; k < NT / 64; k += kByLeg ? Dk : 1) env = cadd(env, part[k][e]);
         const int dl = x > 0 ? Dk : 1, dr = x < L - 1 ? Dk : 1;
-        if (l < dl && r < dr && dd < ddm && u < du) Oy[(size_t)x * P4 + ((l * dr + r) * ddm + dd) * du + u] = env;
+        if (l < dl && r < dr && dd < ddm && u < du) Oy[(size_t)x * P4 + ((l * dr + r) * ddm + dd) * du + u] = cxc{env.re, env.im};
       }
       absorb_columns<Dk, RT, cols<Dk, RT, NT>(), true>(F, F, T + (size_t)x * P4, L, x, true, false);
       __syncthreads();
@@ -1268,12 +1273,13 @@ k_cx_logderiv(Dims d, const double* __restrict__ proj, const uint8_t* __restrict
     if (e < P4)
       for (int x = 0; x < L; ++x) {
         const int dl = x > 0 ? Dk : 1, dr = x < L - 1 ? Dk : 1;
-        cx* Os = Oy + (size_t)x * P4;
+        cxc* Os = Oy + (size_t)x * P4;
         if (l < dl && r < dr && dd < ddm && u < du) {  // written above by this thread
-          cx& o = Os[((l * dr + r) * ddm + dd) * du + u];
-          o = cdiv(o, psi);
+          cxc& o = Os[((l * dr + r) * ddm + dd) * du + u];
+          const cx q = cdiv(o, psi);
+          o = cxc{q.re, q.im};
         }
-        if (e >= dl * dr * ddm * du) Os[e] = cx{0.0, 0.0};  // beyond the block
+        if (e >= dl * dr * ddm * du) Os[e] = cxc{0.0, 0.0};  // beyond the block
       }
     __syncthreads();  // the next item's tensors and states
   }
@@ -1410,7 +1416,7 @@ k_cx_force(Dims d, int B, int nblk, const int64_t* __restrict__ site_offset, con
   const CxParamBlock p = param_block(d, nblk, site_offset, off);
   if (!p.exists) return;
   const int s = blockIdx.x / nblk;
-  const cx* Oc = reinterpret_cast<const cx*>(O);
+  const cxc* Oc = reinterpret_cast<const cxc*>(O);
   const int32_t* li = list + (size_t)s * B;
   cx om{0.0, 0.0}, oe{0.0, 0.0};
   if (p.lane < p.lanes) {
@@ -1511,7 +1517,7 @@ k_cx_ov(Dims d, int k, double rtol2, const int64_t* __restrict__ site_offset, co
   }
   const double beta = rr / sc[kCgRR];  // unused at k = 0
   const int L = d.L, Dk = d.Dk;
-  const cx* Oc = reinterpret_cast<const cx*>(O) + (size_t)b * d.n_sites * d.P4;
+  const cxc* Oc = reinterpret_cast<const cxc*>(O) + (size_t)b * d.n_sites * d.P4;
   const cx* rc = reinterpret_cast<const cx*>(r);
   const cx* pc = reinterpret_cast<const cx*>(p);
   cx acc{0.0, 0.0};
@@ -1521,7 +1527,7 @@ k_cx_ov(Dims d, int k, double rtol2, const int64_t* __restrict__ site_offset, co
     const int bsize = ipow(Dk, (x > 0) + (x < L - 1) + (y > 0) + (y < L - 1));
     if (e >= bsize) continue;
     const int64_t m = site_offset[s] + (int64_t)bid[(size_t)b * d.n_sites + s] * bsize + e;
-    acc = cfma(Oc[i], cg_direction(rc, pc, m, k, beta), acc);
+    acc = cfma(cx(Oc[i]), cg_direction(rc, pc, m, k, beta), acc);
   }
   acc = block_sum_cx(acc, red);
   if (threadIdx.x == 0) {
@@ -1541,13 +1547,13 @@ k_cx_sv(Dims d, int B, int nblk, int k, double rtol2, const int64_t* __restrict_
   const CxParamBlock p = param_block(d, nblk, site_offset, off);
   if (!p.exists) return;
   const int s = blockIdx.x / nblk;
-  const cx* Oc = reinterpret_cast<const cx*>(O);
+  const cxc* Oc = reinterpret_cast<const cxc*>(O);
   const int32_t* li = list + (size_t)s * B;
   cx acc{0.0, 0.0};
   if (p.lane < p.lanes) {
     for (int i = p.first + p.lane; i < p.last; i += p.lanes) {
       const int b = li[i];
-      const cx t = cmul(cconj(Oc[((size_t)b * d.n_sites + s) * d.P4 + p.k]), cx{ov[2 * b], ov[2 * b + 1]});
+      const cx t = cmul(cconj(cx(Oc[((size_t)b * d.n_sites + s) * d.P4 + p.k])), cx{ov[2 * b], ov[2 * b + 1]});
       acc = cadd(acc, cx{w[b] * t.re, w[b] * t.im});
     }
   }

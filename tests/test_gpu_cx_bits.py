@@ -62,3 +62,43 @@ def test_slots_take_the_bytes_of_their_precision(lib, L, Dk, B):
     per_cu, states = (1, L + 2) if W > 2187 else (3, L)
     slots = max(B, min(B * L, per_cu * torch.cuda.get_device_properties(0).multi_processor_count))
     assert abs(n[1] - n[0] - 8 * (B * 2 * (L + 1) * S + slots * states * W)) <= 8 * 256
+
+
+@pytest.mark.parametrize("L,Dk", [(4, 2), (7, 3)])
+def test_buffers_aligned_to_float64_only(lib, L, Dk):
+    # complex numbers are pairs of float64, so theta, proj and O may start at any multiple of 8 bytes
+    import ctypes
+    c, e = config_tables(2, 1.0, 0.4)
+    P, B = lib.Peps(L, 2, Dk, 4, c, e, dtype=lib.PEPS_C128_EXACT), 6
+    rng = np.random.Generator(np.random.PCG64(3))
+    th = torch.from_numpy(1 + 0.3 * (rng.standard_normal(P.n_params) + 1j * rng.standard_normal(P.n_params))).cuda()
+    powers = synth.plaquette_powers(B, L, 2, seed=5)
+    lk = torch.from_numpy(np.stack([links_from_powers(powers[b], 2) for b in range(B)])).cuda()
+    what = lib.PEPS_WS_AMPLITUDE | lib.PEPS_WS_TVMC
+
+    def run(shift):
+        ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+        room = lambda n: torch.zeros(2 * n + 1, dtype=torch.float64, device="cuda")[shift:shift + 2 * n]
+        n = B * L * L * Dk ** 4
+        theta, proj, O, el, x = room(P.n_params), room(n), room(n), room(B), room(P.n_params)
+        theta.copy_(torch.view_as_real(th).reshape(-1))
+        assert all(t.data_ptr() % 16 == 8 * shift for t in (theta, proj, O, el, x))
+        bid = torch.zeros(B * L * L, dtype=torch.int32, device="cuda")
+        valid = torch.zeros(B, dtype=torch.uint8, device="cuda")
+        la, ph = torch.zeros(B, dtype=torch.float64, device="cuda"), room(B)
+        ws = P.workspace(B, what)
+        f, h, s = lib.lib(), P._h, None
+        w = (ptr(ws), ws.numel(), s)
+        assert f.peps_cx_project(h, ptr(theta), ptr(lk), B, ptr(proj), ptr(bid), ptr(valid), s) == 0
+        assert f.peps_cx_amplitude(h, ptr(proj), ptr(valid), B, ptr(la), ptr(ph), *w) == 0
+        assert f.peps_cx_logderiv(h, ptr(proj), ptr(valid), B, ptr(O), *w) == 0
+        assert f.peps_cx_local_energy(h, ptr(theta), ptr(lk), ptr(proj), ptr(valid), B, ptr(el), *w) == 0
+        en, it, rel = (ctypes.c_double * 2)(), ctypes.c_int32(), ctypes.c_double()
+        assert f.tvmc_rhs(h, ptr(O), ptr(bid), ptr(valid), ptr(el), ptr(la), B, 0, 0.05, 20, 1e-8, ptr(x), en,
+                          ctypes.byref(it), ctypes.byref(rel), *w) == 0
+        torch.cuda.synchronize()
+        return [t.cpu().numpy().view(np.uint64) for t in (proj, la, ph, O, el, x)]
+
+    torch.cuda.synchronize()
+    for a, b in zip(run(0), run(1)):
+        assert np.array_equal(a, b)

@@ -282,7 +282,7 @@ int peps_amplitude(peps_handle* h, const double* proj, const uint8_t* valid, int
  * 1 <= n <= 8; all handles real, of one dtype and D_k = 2, without keep_tape or var_sweeps
  * (PEPS_ERR_UNSUPPORTED otherwise), either all or none with fused bonds above 72; each ws[i]
  * sized for h[i] with PEPS_WS_AMPLITUDE (checked, PEPS_ERR_WORKSPACE).  The row kernel is the one
- * selected by the largest fused bond of the groups, with the Jacobi lanes, waves and
+ * selected by the largest fused bond of the groups, with the Jacobi lanes and
  * preconditioning of h[0]'s tuning: a group whose own kernel differs gets ln|Psi| equal to its
  * peps_amplitude result up to rounding (identical bits where the kernels agree).  Afterwards each
  * ws[i] is in the state peps_amplitude leaves (peps_local_energy / peps_logderiv may follow on it).
@@ -341,7 +341,7 @@ int peps_logderiv(peps_handle* h, const double* proj, const int32_t* block_id,
  * mode SR_DENSE:  v unused, S_or_Sv float64 [n_params][n_params] row-major = S; only for
  *                 n_params <= 8192 (PEPS_ERR_UNSUPPORTED otherwise).
  * ws: the workspace of peps_workspace_bytes(..., PEPS_WS_LOGDERIV) (uses B + 8 doubles of it).
- * Reductions run over samples in index order: results are bitwise reproducible. */
+ * Reductions run over samples in a fixed order: results are bitwise reproducible. */
 int sr_build(peps_handle* h, const double* O, const int32_t* block_id, const uint8_t* valid,
              const double* e_loc, int32_t B, int32_t mode, const double* v, double* F,
              double* O_mean, double* S_or_Sv, void* ws, size_t ws_bytes, void* stream);
@@ -390,11 +390,13 @@ int peps_eloc_scale(peps_handle* h, int32_t B, const void* ws, size_t ws_bytes, 
 /* Tuning of the boundary row sweep (the kernel that dominates every call).  None of these choices
  * changes the result beyond rounding: the truncated boundary depends only on the state, and every
  * choice is parity-tested against the oracle.
- *   jacobi_lanes  lanes per column pair in the one-sided Jacobi SVD: 4 or 8
- *   down_precond  large SVDs of the down sweeps (peps_amplitude; reversed by peps_logderiv):
+ *   jacobi_lanes  lanes per column pair in the one-sided Jacobi SVD: 4 or 8 (fused bonds up to 72)
+ *   down_precond  large SVDs of the sweeps that peps_logderiv may reverse (peps_amplitude and its
+ *                 variants):
  *                 PEPS_PRECOND_NONE or PEPS_PRECOND_SORTED_QR (columns sorted by norm, QR, Jacobi on
  *                 R^T: the left vectors stay accumulated, as the reverse sweep needs)
- *   up_precond    large SVDs of the up sweeps (peps_local_energy, peps_metropolis_strip):
+ *   up_precond    large SVDs of the sweeps that are never reversed (the up sweeps of peps_local_energy,
+ *                 every boundary of peps_metropolis_strip but that of its final amplitude):
  *                 PEPS_PRECOND_NONE, PEPS_PRECOND_QR_T (QR of Theta^T, Jacobi on R^T) or
  *                 PEPS_PRECOND_SORTED_QR
  *   precond_min   a cut is preconditioned when Theta is wide or square and its smaller dimension is
@@ -407,7 +409,7 @@ typedef struct {
   int32_t jacobi_lanes, down_precond, up_precond, precond_min, small_waves;
 } peps_tuning;
 /* One timed candidate of peps_autotune: a down (up = 0) or up (up = 1) sweep with the given lanes,
- * preconditioning mode, threshold and waves, ms its duration (HIP events on the stream). */
+ * preconditioning mode and threshold, ms its duration (HIP events on the stream). */
 typedef struct {
   int32_t jacobi_lanes, precond, precond_min, small_waves, up;
   double ms;

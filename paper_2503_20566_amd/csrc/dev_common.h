@@ -60,8 +60,8 @@ __device__ inline double block_sum(double v, double* red) {
   return s;
 }
 
-// Quotients by a number that is known at run time only, by a product: exact for e d < 2^32 (e < 2^14 and
-// d < 2^14 here).  The division itself is some forty instructions, more than an element's own work.
+// Quotients by a number that is known at run time only, by a product: exact for e d < 2^32 (e up to
+// 2^15 and d up to 2^8 here).  The division itself is some forty instructions, more than an element's own work.
 struct FastDiv {
   unsigned d, m;
   __device__ explicit FastDiv(int div) : d((unsigned)div), m(0xFFFFFFFFu / (unsigned)div + 1u) {}

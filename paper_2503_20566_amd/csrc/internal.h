@@ -40,7 +40,7 @@ struct Dims {
   // tuning of the row sweep (peps_tuning): Jacobi lanes per column pair, preconditioning of the
   // down (reversible) and up sweeps' large SVDs, smallest cut dimension that is preconditioned
   int jacobi_lanes, down_precond, up_precond, precond_min;
-  int small_waves;  // waves per SIMD of the chi*Dk <= 32 row-sweep kernels: 2 or 4
+  int small_waves;  // 2 or 4, kept for peps_get_tuning: no kernel depends on it
   int var_sweeps;   // variational compression: fitting sweeps after each row's SVD truncation (0: none)
   int matter;       // 1: hard-core bosons on the vertices (occupation plane in the configuration)
   int planes;       // planes of a configuration: 2 (links) or 3 (links + occupations)
@@ -110,7 +110,7 @@ struct WsLayout {
   size_t rowtmp;    // double [B][row_stride]         recomputed boundary row
   size_t lognu2;    // double [B][L]                  ln nu of recomputed rows (unused values)
   size_t seg;       // double [ckpt][B][row_stride]   rows recomputed from a checkpoint
-  size_t sr;        // double [B + 8]                 sr_build: (O v)_b and <O>.v
+  size_t sr;        // double [B + 8]                 sr_build, sr_solve: (O v)_b
   size_t cg;        // double [3 n_params + 2 (kMaxCgIter + 2)]  sr_solve: r, p, q and CG scalars
   size_t flag;      // uint32 [4]                     state flags written by the host
   size_t status;    // uint32 [B]                     per-sample PEPS_FLAG_* bits
@@ -179,7 +179,7 @@ struct RaggedRows {
   int n;
   RaggedRow g[kMaxRagged];
 };
-// maxN: largest fused bond over the groups (selects the instantiation); mixed, lanes, waves,
+// maxN: largest fused bond over the groups (selects the instantiation); mixed, lanes,
 // precondition settings: taken from `tune` (the first group's handle)
 hipError_t launch_row_sweep_ragged(const RaggedRows& r, int total_blocks, int y, int Dk, int maxN,
                                    const Dims& tune, hipStream_t s);

@@ -2,8 +2,9 @@
 // <O E> - <O><E>; SM S-3 S_mn = <O_m O_n> - <O_m><O_n>; plain means over the valid samples).
 //
 // O arrives block-sparse: per sample and site only the selected block is nonzero, stored in the
-// projected layout with its block index.  Every kernel here reduces over samples in index order
-// (no atomics), so results are bitwise reproducible.
+// projected layout with its block index.  Every kernel here reduces over samples in a fixed
+// order (no atomics; k_sr_blocks by lane groups, the dense forms in index order), so results are bitwise
+// reproducible.
 //   k_sr_blocks : per site and block: <O> and F, or S v = <O (O v)> - <O> (<O> . v), or the vjp
 //   k_sr_ov     : (O v)_b per sample (gathers v through the block index)
 //   k_cg_*      : the vector steps of the conjugate gradients, their dot products in block partials

@@ -32,8 +32,9 @@
 
 namespace gipeps {
 
-// Every multiply-add below is written as fma where it is one: the batch and the ragged kernel, and the same
-// bonds in another class, must give the same bits, whatever the compiler would contract in each.
+// Every multiply-add below is written as fma where it is one: the batch and the ragged kernel of a class must
+// give the same bits, whatever the compiler would contract in each.  (Classes agree to rounding: the partial
+// sums of a reflector's dot products follow the rows per lane.)
 #pragma clang fp contract(off)
 
 // Largest matrices (fused bond) of each instantiation, its threads and the waves per SIMD it is compiled
@@ -862,8 +863,8 @@ __device__ __forceinline__ bool jacobi_svd(double* A, int nr, int nc, double* J,
 // (TapeSlot layout) for the adjoint.
 // ---------------------------------------------------------------------------------------------
 // pmode: preconditioning of the large truncated SVDs (cuts whose Theta is wide or square with at least
-// pthr rows): PEPS_PRECOND_NONE, PEPS_PRECOND_QR_T (sweeps that are never
-// reversed) or // PEPS_PRECOND_SORTED_QR; see the forms of the SVD below.
+// pthr rows): PEPS_PRECOND_NONE, PEPS_PRECOND_QR_T (sweeps that are never reversed) or
+// PEPS_PRECOND_SORTED_QR; see the forms of the SVD below.
 // The row step of sample b, shared by the batch kernel (one lattice) and the ragged kernel (several
 // lattices in one launch).  qslot: doubles per (sample, site) Q-factor slot of qscr.
 // tslot: doubles per (sample, site) tape slot.
@@ -1046,7 +1047,7 @@ __device__ __forceinline__ void row_sweep_body(const Dims& d, const int* __restr
   //             72 x 72 Theta);
   //   QR_T      (large cuts with PEPS_PRECOND_QR_T) Theta^T = Q_x R_x, Jacobi on R_x^T: the columns are
   //             the left vectors, V = Q_x J; 6.5 sweeps.  Only for sweeps that are never reversed (the
-  //             up sweeps): a left vector of singular value s from a column carries an error
+  //             up sweeps, the strip sampler's): a left vector of singular value s from a column carries an error
   //             ~ eps ||Theta|| / s, which the truncated-SVD backward would amplify by 1 / s_kept through
   //             the kept-discarded terms (Euler identity off by 4e-9 instead of ~1e-13); the kept
   //             vectors are unaffected.
@@ -1249,8 +1250,8 @@ k_row_sweep_ragged(RaggedRows r, int y, int pmode, int pthr) {
                                    (int)blockIdx.x - g.first_block);
 }
 
-// Launches of one class (instantiated in the k_row_*.hip files).  The large bonds always run four
-// Jacobi lanes per column pair (the J rows need the other half of the workgroup).
+// Launches of one class (instantiated in the k_row_*.hip files).  The large bonds always run
+// eight Jacobi lanes per group of four columns (jacobi_columns).
 template <int MAXN, int DK, typename CT, int GW>
 hipError_t launch_row_t(const RowArgs& a, hipStream_t s) {
   const dim3 grid(a.blocks), blk(RowCfg<MAXN>::NT);

@@ -1124,15 +1124,18 @@ int cx_rhs(peps_handle* h, const gipeps::CxWs& w, char* base, const double* O, c
     });
   // conjugate gradients for (S + shift I) y = g from y = 0 (Hermitian inner products).  The kernels of an
   // iteration past the end do nothing, so the host looks at the scalars once in kCheck iterations: with two
-  // readbacks in each, the device was idle for 50 of an iteration's 108 us.
+  // readbacks in each, the device was idle for 50 of an iteration's 108 us.  A loose tolerance is met within a
+  // few iterations, and its empty ones up to the eighth took longer than a readback, hence a first look after two
+  // (4 x 4, 64 samples, rtol 0.3: 0.19 -> 0.13 ms; at rtol 1e-8 the further readback would cost 50 us of 420).
   constexpr int kCheck = 8;
+  const int first = rtol >= 1e-2 ? 2 : kCheck;
   if (e == hipSuccess) e = launch_cx_cg_start(n, g, y, r, sc, s);
   double state[kCxScalars] = {};
   double rr = 0.0, f2 = 0.0;
   int k = 0;
   bool done = false;
   for (int next = 0; e == hipSuccess;) {
-    for (const int last = std::min(max_iter, next + kCheck); next < last && e == hipSuccess; ++next)
+    for (const int last = std::min(max_iter, next + (next == 0 ? first : kCheck)); next < last && e == hipSuccess; ++next)
       e = timed(h, PEPS_K_SR, s, [&] {
         return launch_cx_cg_iteration(h->d, h->t, n, B, bid, ioff, ilist, wt, O, omean, shift, next, rtol * rtol, y, r,
                                       p, q, ov, sc, s);

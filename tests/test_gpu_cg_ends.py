@@ -6,12 +6,16 @@ Every number is exact.  Four samples give two parameters of one block a diagonal
 smallest number.  E = +-2 e_0 and +-2^541 e_1 make the force (e_0, e_1), with <O> = <E> = 0.  From (1, 1): q = (1/2, 0),
 alpha = 2 / (1/2) = 4, x = (4, 4), r = (-1, 1), beta = 1, p = (0, 2), and S p = 0 ends it after one iteration with r.r
 what it was.
+
+The complex solver reads its state back after 8 iterations, after 2 at a tolerance of at least 1e-2, and then every 8:
+tolerances of either kind, met at, before and after the first readbacks.
 """
 import numpy as np
 import pytest
 import torch
 
 from oracle.energy import config_tables
+from tests.test_gpu_cx_cg import cg, check, system  # noqa: F401  (system: the fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +58,14 @@ def test_ends(lib, cplx, e0, e1, max_iter, its, rel, x0, x1):
     x, got_its, got_rel = solve(lib, cplx, e0, e1, max_iter)
     assert (got_its, got_rel) == (its, rel)
     assert x[0] == x0 and x[1] == x1 and not x[2:].any()
+
+
+@pytest.mark.parametrize("rtol", [0.5, 0.1, 1e-2, 0.99e-2, 1e-3, 1e-5])
+@pytest.mark.parametrize("limit", [1, 2, 3, 200])
+def test_tolerances_around_the_readbacks(system, rtol, limit):  # noqa: F811
+    P, args, S, g = system
+    _, res = cg(S, g, 40)
+    met = next(i for i, r in enumerate(res) if r <= rtol ** 2 * res[0])
+    assert all(abs(r / (rtol ** 2 * res[0]) - 1) > 1e-6 for r in res), "a residual too close to the bound to tell"
+    rel = check(P, args, S, g, min(met, limit), max_iter=limit, rtol=rtol)
+    assert (rel <= rtol) == (met <= limit)

@@ -31,22 +31,23 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X FP64 vector: 256 CU x 2.4 GHz x 128 fl
 # HBM bytes per k_row_sweep launch at z3_16x16_d6 (mean over the step's 27 launches: 14 taped
 # down-sweep rows, 13 up-sweep rows) from rocprofv3 FETCH_SIZE / WRITE_SIZE runs, scaled by a
 # plain-copy calibration (FETCH x2.00, WRITE x1.00); valid only for the kernel source and build
-# flags they were measured with (sha256 prefixes of k_sweep.hip, dev_common.h and build.py),
+# flags they were measured with (sha256 prefixes of the files that hold the kernel and its flags),
 # reported as null otherwise.
-ROW_SWEEP_TRAFFIC = {"sources": {"csrc/k_sweep.hip": "8bf47d09c6b23d74", "csrc/dev_common.h": "dc494028c62ca1a2",
-                                 "build.py": "f7ebea33db24a875"},
-                     "workload": "z3_16x16_d6", "bytes": 1058784 * 1024 * 2.00 + 2021970 * 1024 * 1.00}
+ROW_SWEEP_SOURCES = {"csrc/row_sweep.h": "1ae23d85798b9995", "csrc/jacobi_scalar.h": "98eb1cb16f6a5b54",
+                     "csrc/dev_common.h": "dbadecc1fef6d080", "csrc/k_row_72.hip": "d6444623aa9c4da7",
+                     "build.py": "f7ebea33db24a875"}
+ROW_SWEEP_TRAFFIC = {"sources": ROW_SWEEP_SOURCES,
+                     "workload": "z3_16x16_d6", "bytes": 743221 * 1024 * 2.00 + 1919140 * 1024 * 1.00}
 
 
 # Executed FP64 work per k_row_sweep launch at z3_16x16_d6 from rocprofv3 counters
 # (profiles/pmc_fp64_mfma_z3_16x16_d6.md): 64 x SQ_INSTS_VALU_FLOPS_FP64(+_TRANS) (per-wave counts,
 # FMA = 2) + 512 x SQ_INSTS_VALU_MFMA_MOPS_F64, and the MfmaUtil / VALUBusy / LdsUtil percentages;
 # valid only for the kernel source and build flags they were measured with.
-ROW_SWEEP_EXECUTED = {"sources": {"csrc/k_sweep.hip": "8bf47d09c6b23d74", "csrc/dev_common.h": "dc494028c62ca1a2",
-                                  "build.py": "f7ebea33db24a875"},
+ROW_SWEEP_EXECUTED = {"sources": ROW_SWEEP_SOURCES,
                       "workload": "z3_16x16_d6",
-                      "flops": 64 * (4.7527e9 + 5.9116e7) + 512 * 3.7085e7,
-                      "mfma_util_pct": 0.64, "valu_busy_pct": 29.0, "lds_util_pct": 21.9}
+                      "flops": 64 * (3.9701e9 + 5.8671e7) + 512 * 3.7085e7,
+                      "mfma_util_pct": 0.79, "valu_busy_pct": 30.2, "lds_util_pct": 22.9}
 
 
 def _sources_match(sources):

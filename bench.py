@@ -668,8 +668,8 @@ def main():
         ragged_run(args.steps)
         return
     if args.gpus != 1:
-        print("bench.py measures one GPU only: every box here has a single MI355X and this "
-              "path shards by samples (see the design notes); run with --gpus 1", file=sys.stderr)
+        print("bench.py measures one GPU only: the path shards by samples "
+              "(see the design notes); run with --gpus 1", file=sys.stderr)
         sys.exit(2)
 
     from paper_2503_20566_amd import synth
